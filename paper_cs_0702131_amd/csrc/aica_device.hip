@@ -91,6 +91,7 @@ struct aica_dil {
   std::vector<uint8_t> split_depth;  // k-d tree of the sorted order (groups are its subtrees)
   std::vector<CellPair> pairs;
   double rcut = 0, guard = 0, build_seconds = 0, group_seconds = 0;
+  int32_t predicate = AICA_DIL_CLOSEST;
   int device = 0;
   bool geometry_on_device = false;
   // device geometry for point location (mesh cell ids)
@@ -107,10 +108,14 @@ struct aica_dil {
   int64_t groups_for_n = -1;
   Groups grp;
   DBuf d_orig, d_g_cell0, d_e_off, d_e_B, d_e_vec32, d_e_vec64, d_nl_off, d_nl_e, d_nl_d, d_nl_r, d_rcnt;
+  // full neighbour lists of the force kernel (its own groups; same lifetime)
+  Neigh nb;
+  DBuf d_nb_cell0, d_nb_run_off, d_nb_runs, d_nb_eB, d_nb_erev, d_nb_vec32, d_nb_vec64, d_nb_orig, d_nb_eoff;
+  DBuf d_box;                   // [groups][6] box of each group's molecules in its frame (compute type)
   DBuf d_rot64;                 // [27][9] rotation of every image code (only with rotational referral)
   // per step
   bool bin_valid = false;
-  bool wsteps_valid = false;  // d_gnp holds the wave-step counts of a forward call on the current binning
+  int64_t wsteps_groups = 0;  // groups whose wave-step counts d_gnp holds (a forward call on the current binning)
   int64_t n = 0;
   const void *bin_pos = nullptr;
   int32_t bin_dtype = 0;
@@ -739,14 +744,76 @@ __global__ void k_gather(const PT *__restrict__ pos, const int32_t *__restrict__
   out[m] = v;
 }
 
+// Gather by groups, one wave each: positions in cell-sorted order relative to the group's origin (species id in .w as
+// integer bits), and the box of the group's molecules (empty: lo > hi).
+template <typename T, typename PT>
+__global__ __launch_bounds__(256) void k_gather_groups(const PT *__restrict__ pos, const int32_t *__restrict__ species,
+                                                       const int32_t *__restrict__ perm,
+                                                       const int32_t *__restrict__ cell_start,
+                                                       const int32_t *__restrict__ cell0, const double *__restrict__ orig,
+                                                       int64_t ng, int nsp, typename Vec4<T>::type *__restrict__ out,
+                                                       T *__restrict__ box) {
+  const int lane = threadIdx.x & 63;
+  const int64_t a = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (a >= ng) return;
+  const int32_t m0 = cell_start[cell0[a]], m1 = cell_start[cell0[a + 1]];
+  const double o[3] = {orig[3 * a], orig[3 * a + 1], orig[3 * a + 2]};
+  T lo[3] = {(T)1e30, (T)1e30, (T)1e30}, hi[3] = {(T)-1e30, (T)-1e30, (T)-1e30};
+  for (int32_t m = m0 + lane; m < m1; m += 64) {
+    const int64_t id = perm[m];
+    T x[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      x[k] = (T)((double)pos[3 * id + k] - o[k]);
+      lo[k] = min(lo[k], x[k]);
+      hi[k] = max(hi[k], x[k]);
+    }
+    const int32_t t = species ? min(max(species[id], 0), nsp - 1) : 0;  // out-of-range ids are clamped
+    typename Vec4<T>::type v;
+    v.x = x[0];
+    v.y = x[1];
+    v.z = x[2];
+    if constexpr (sizeof(T) == 4)
+      v.w = __builtin_bit_cast(float, t);
+    else
+      v.w = __builtin_bit_cast(double, (int64_t)t);
+    out[m] = v;
+  }
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      lo[k] = min(lo[k], __shfl_xor(lo[k], s, 64));
+      hi[k] = max(hi[k], __shfl_xor(hi[k], s, 64));
+    }
+  if (lane == 0)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      box[6 * a + k] = lo[k];
+      box[6 * a + 3 + k] = hi[k];
+    }
+}
+
 struct LJTab {
   float sig2[64], e24[64], e4[64];
   double sig2d[64], e24d[64], e4d[64];
   float rc2, band;
   float rc2lo, rc2hi;  // rc^2 -+ band: an FP32 s below rc2lo is surely inside, at or above rc2hi surely outside
   double rc2d;
+  // rc^2 -+ the most that the two sides of a pair can differ by in its square (rounding of positions referred
+  // between group frames, and of the square): in between, both sides take the canonical side's decision
+  float near_lo, near_hi;
+  double near_lod, near_hid;
   int nsp;
 };
+template <typename T>
+__device__ __forceinline__ T near_lo(const LJTab &t) {
+  if constexpr (sizeof(T) == 4) return t.near_lo; else return t.near_lod;
+}
+template <typename T>
+__device__ __forceinline__ T near_hi(const LJTab &t) {
+  if constexpr (sizeof(T) == 4) return t.near_hi; else return t.near_hid;
+}
 
 template <typename T>
 __device__ __forceinline__ int type_of(T w) {
@@ -833,6 +900,7 @@ __device__ __forceinline__ T far_j() { return (T)-1e15; }
 }  // namespace
 
 #include "aica_pair.inc"
+#include "aica_neigh.inc"
 #include "aica_adjoint_pair.inc"
 
 namespace {
@@ -894,7 +962,7 @@ __device__ void reduce_part_rows(const double *part, int nb, double *out) {
 
 // U, W (FP64) and the pair count from the stage-1 rows (U, W) and (npairs).
 __global__ __launch_bounds__(kRedThreads) void k_reduce_uw(const double *part_uw, const double *part_np, int nb,
-                                                            double *uw, int64_t *npairs) {
+                                                            double *uw, int64_t *npairs, int sides) {
   double a[2], c[1];
   reduce_part_rows<2>(part_uw, nb, a);
   __syncthreads();
@@ -904,7 +972,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_uw(const double *part_uw
       uw[0] = a[0];
       uw[1] = a[1];
     }
-    if (npairs) npairs[0] = (int64_t)c[0];
+    if (npairs) npairs[0] = (int64_t)c[0] / sides;
   }
 }
 
@@ -1205,6 +1273,54 @@ static int ensure_groups(aica_dil *h, int64_t n) {
     if ((rc = upload(h->d_rcnt, rcnt))) return rc;
   }
   if ((rc = upload(h->d_orig, G.orig))) return rc;
+  // the force kernel's neighbour lists
+  double nb_target = 128.0;
+  if (const char *e = getenv("AICA_NB_TARGET")) nb_target = std::max(1.0, atof(e));
+  if ((rc = build_neigh(h->geo, h->order, h->split_depth, h->pairs, h->predicate == AICA_DIL_VERTEX, density, nb_target, h->nb)))
+    return rc;
+  {
+    const Neigh &N = h->nb;
+    const int64_t NE = N.e_off[N.ng];
+    v32.resize(NE);
+    v64.resize(NE);
+    parallel_for(N.ng, [&](int64_t b, int64_t e, int) {
+      for (int64_t a = b; a < e; ++a)
+        for (int64_t k = N.e_off[a]; k < N.e_off[a + 1]; ++k) {
+          const int64_t B = N.e_B[k];
+          const int c = N.e_code[k];
+          const Xf T = image_transform(h->geo, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
+          double o[3], tb[3] = {0, 0, 0};
+          if (T.rot) T.apply(&N.orig[3 * B], tb);
+          for (int q = 0; q < 3; ++q)
+            o[q] = T.rot ? tb[q] - N.orig[3 * a + q] : N.orig[3 * B + q] + T.y[q] - N.orig[3 * a + q];
+          const int code = c + (T.rot ? kRotFlag : 0);
+          v32[k] = make_float4((float)o[0], (float)o[1], (float)o[2], __builtin_bit_cast(float, code));
+          v64[k] = make_double4(o[0], o[1], o[2], __builtin_bit_cast(double, (int64_t)code));
+        }
+    });
+    if ((rc = upload(h->d_nb_cell0, N.cell0))) return rc;
+    if ((rc = upload(h->d_nb_run_off, N.run_off))) return rc;
+    if ((rc = upload(h->d_nb_runs, N.runs))) return rc;
+    if ((rc = upload(h->d_nb_eB, N.e_B))) return rc;
+    if ((rc = upload(h->d_nb_eoff, N.e_off))) return rc;
+    if ((rc = upload(h->d_nb_erev, N.e_rev))) return rc;
+    if ((rc = upload(h->d_nb_vec32, v32))) return rc;
+    if ((rc = upload(h->d_nb_vec64, v64))) return rc;
+    if ((rc = upload(h->d_nb_orig, N.orig))) return rc;
+    if (getenv("AICA_VERBOSE"))
+      fprintf(stderr, "neighbour lists: %lld groups, %lld entries, %lld runs, reach %.3f\n", (long long)N.ng, (long long)NE,
+              (long long)N.runs.size(), N.reach);
+    if (getenv("AICA_VERBOSE")) {
+      double vol = 0, cells = 0;
+      for (const CellRun &r : N.runs)
+        for (int32_t s = r.d0; s < r.d1; ++s) {
+          vol += h->geo.vol[h->order[s]];
+          cells += 1;
+        }
+      fprintf(stderr, "neighbour lists: per group %.1f runs, %.1f cells, %.1f molecules expected\n", (double)N.runs.size() / N.ng,
+              cells / N.ng, vol * density / N.ng);
+    }
+  }
   h->groups_ready = true;
   h->groups_for_n = n;
   h->group_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -1237,6 +1353,7 @@ int aica_build_dil_ex(const aica_mesh *mesh, double rcut, double guard, int32_t 
   }
   h->rcut = rcut;
   h->guard = guard;
+  h->predicate = predicate;
   const bool verbose = getenv("AICA_VERBOSE") != nullptr;
   auto t1 = std::chrono::steady_clock::now();
   spatial_order(h->geo, h->order, h->rank, h->split_depth);
@@ -1268,7 +1385,7 @@ void aica_dil_free(aica_dil *h) {
 int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, void *hip_stream) {
   if (!h) return fail(AICA_E_INVAL, "handle is NULL");
   h->bin_valid = false;
-  h->wsteps_valid = false;
+  h->wsteps_groups = 0;
   if (n < 0 || (n > 0 && !pos_dev)) return fail(AICA_E_INVAL, "bad positions");
   if (n >= (1LL << 28) - 1) return fail(AICA_E_INVAL, "too many molecules (the pair kernels take fewer than 2^28 - 1)");
   if (pos_dtype != AICA_FP32 && pos_dtype != AICA_FP64) return fail(AICA_E_INVAL, "pos_dtype must be AICA_FP32 or AICA_FP64");
@@ -1406,17 +1523,32 @@ static int build_tab(const aica_dil *h, const aica_params *p, LJTab &t) {
   t.band = (float)(t.rc2d * std::ldexp(1.0, -20));
   t.rc2lo = (float)(t.rc2d - (double)t.band);
   t.rc2hi = (float)(t.rc2d + (double)t.band);
+  // per axis a referred position is rounded by at most half an ulp of reach on either side of the pair
+  auto near = [&](double half_ulp) { return 8.0 * p->rcut * h->nb.reach * half_ulp + 16.0 * t.rc2d * half_ulp; };
+  t.near_lo = (float)(t.rc2d - near(std::ldexp(1.0, -24)));
+  t.near_hi = (float)(t.rc2d + near(std::ldexp(1.0, -24)));
+  t.near_lod = t.rc2d - near(std::ldexp(1.0, -53));
+  t.near_hid = t.rc2d + near(std::ldexp(1.0, -53));
   t.nsp = p->n_species;
   return AICA_OK;
 }
 
 // Device buffers of one force call: the handle's grow-only workspace, or regions of the fixed scratch array
-// (aica_forces_noalloc).  pos: [n] gathered positions; own: [2n] (hi, lo) own records; jpart: [J] reaction
-// records tagged with epoch; gpart, gnp: per-group partials; red: stage-1 reduction rows.
+// (aica_forces_noalloc).  pos: [n] gathered positions; box: the groups' boxes (full lists); own: [2n] (hi, lo) own
+// records and jpart: [J] reaction records tagged with epoch (half lists); gpart, gnp: per-group partials; red: stage-1
+// reduction rows.
 struct ForceWs {
-  void *pos = nullptr, *own = nullptr, *jpart = nullptr, *gpart = nullptr, *gnp = nullptr, *red = nullptr;
+  void *pos = nullptr, *box = nullptr, *own = nullptr, *jpart = nullptr, *gpart = nullptr, *gnp = nullptr, *red = nullptr;
   uint32_t epoch = 0;
 };
+
+// Which lists a force call runs on.  The full lists (k_force: every pair from both sides, no reaction records) take
+// FP64, and FP32 from 200,000 molecules on: the channel's 6.7M molecules take 1.65 ms in place of 2.50 ms (pair
+// kernel) and 0.34 ms (finalize), a step (bin, forces, adjoint) of the 219,488-molecule mixture 0.50 ms in place of
+// 0.60.  Below that, and with rotating referral, FP32 keeps the half lists: U and W are sums of FP32 terms whose
+// partial sums round to about 1e-9 of the result at 1e4 to 1e5 molecules (at 4e5 across a rotation, where U and W
+// cancel more), and with the half lists they keep the tile-wise partial sums they had.
+static bool full_lists(const aica_dil *h, int tsize) { return tsize == 8 || (h->n >= 200000 && !h->geo.has_rot); }
 
 // Reaction buffer: (re)allocate, fill with a pattern no epoch can equal, and advance the epoch.
 static int prepare_jpart(aica_dil *h, size_t bytes, hipStream_t st) {
@@ -1437,6 +1569,7 @@ static int prepare_jpart(aica_dil *h, size_t bytes, hipStream_t st) {
   return AICA_OK;
 }
 
+// The half-list pair kernel: FP32 forces (MODE 0), pair export and per-molecule counts (MODE 1).
 template <typename T, int MODE>
 static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool comp, hipStream_t st, int64_t cap,
                        unsigned long long *pcount, int32_t *mol_count = nullptr) {
@@ -1482,6 +1615,50 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
   return AICA_OK;
 }
 
+// The force kernel: one block per group of the full neighbour lists.
+template <typename T>
+static int launch_force(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool comp, void *out, hipStream_t st) {
+  using V4 = typename Vec4<T>::type;
+  const int64_t ng = h->nb.ng, padded = ((ng + 7) / 8) * 8;
+  const bool rot = h->geo.has_rot;
+  NbLists nl;
+  nl.cell0 = h->d_nb_cell0.as<int32_t>();
+  nl.run_off = h->d_nb_run_off.as<int64_t>();
+  nl.runs = h->d_nb_runs.as<int4>();
+  nl.e_off = h->d_nb_eoff.as<int64_t>();
+  nl.e_B = h->d_nb_eB.as<int32_t>();
+  nl.e_rev = h->d_nb_erev.as<int32_t>();
+  nl.e_vec = sizeof(T) == 4 ? h->d_nb_vec32.p : h->d_nb_vec64.p;
+  nl.e_vec64 = h->d_nb_vec64.as<double4>();
+  nl.rot = rot ? h->d_rot64.as<double>() : nullptr;
+  nl.ng = ng;
+#define AICA_FORCE(MIX, COMP, ROT)                                                                                  \
+  hipLaunchKernelGGL((k_force<T, MIX, COMP, ROT>), dim3((unsigned)padded), dim3(kNbThreads), 0, st, nl,             \
+                     (const V4 *)ws.pos, (const T *)ws.box, h->d_cell_start.as<int32_t>(), h->d_perm.as<int32_t>(),  \
+                     padded, tab, (T *)out,                                                                           \
+                     (double *)ws.gpart, (unsigned long long *)ws.gnp)
+  const int nsp = tab.nsp;
+  constexpr bool C = sizeof(T) == 4;  // compensated sums exist in FP32 only
+  if (rot) {  // rotating referral: FP64 only (full_lists)
+    if constexpr (sizeof(T) == 8) {
+      if (nsp == 1) AICA_FORCE(0, false, true);
+      else if (nsp == 2) AICA_FORCE(1, false, true);
+      else AICA_FORCE(2, false, true);
+    }
+  } else if (C && comp) {
+    if (nsp == 1) AICA_FORCE(0, C, false);
+    else if (nsp == 2) AICA_FORCE(1, C, false);
+    else AICA_FORCE(2, C, false);
+  } else {
+    if (nsp == 1) AICA_FORCE(0, false, false);
+    else if (nsp == 2) AICA_FORCE(1, false, false);
+    else AICA_FORCE(2, false, false);
+  }
+#undef AICA_FORCE
+  HIPCHK(hipGetLastError());
+  return AICA_OK;
+}
+
 // The adjoint pair kernel (one, two, or three to eight species).
 template <typename T>
 static int launch_adj(aica_dil *h, const LJTab &tab, const AdjTab &at, hipStream_t st) {
@@ -1522,7 +1699,7 @@ static void launch_finalize(aica_dil *h, const ForceWs &ws, void *out, hipStream
                      ws.epoch);
 }
 
-// Gather the binned positions into cell-sorted SoA at dst ([n] V4 of the compute type).
+// Gather the binned positions into cell-sorted SoA (half lists) at dst ([n] V4 of the compute type).
 template <typename T>
 static int gather_to(aica_dil *h, const void *pos_dev, const int32_t *species, int tab_nsp, hipStream_t st, void *dst) {
   using V4 = typename Vec4<T>::type;
@@ -1547,17 +1724,42 @@ static int gather(aica_dil *h, const void *pos_dev, const int32_t *species, int 
   return gather_to<T>(h, pos_dev, species, tab_nsp, st, h->d_pos.p);
 }
 
+// Gather the binned positions by the groups of the full lists into pos, and their boxes into box.
+template <typename T>
+static int gather_groups(aica_dil *h, const void *pos_dev, const int32_t *species, int nsp, hipStream_t st, void *pos,
+                         void *box) {
+  using V4 = typename Vec4<T>::type;
+  const int64_t ng = h->nb.ng;
+#define AICA_GATHER(PT)                                                                                               \
+  hipLaunchKernelGGL((k_gather_groups<T, PT>), dim3(grid1d(ng, 4)), dim3(256), 0, st, (const PT *)pos_dev, species,   \
+                     h->d_perm.as<int32_t>(), h->d_cell_start.as<int32_t>(), h->d_nb_cell0.as<int32_t>(),             \
+                     h->d_nb_orig.as<double>(), ng, nsp, (V4 *)pos, (T *)box)
+  if (h->bin_dtype == AICA_FP64) AICA_GATHER(double);
+  else AICA_GATHER(float);
+#undef AICA_GATHER
+  HIPCHK(hipGetLastError());
+  return AICA_OK;
+}
+
 // The handle's grow-only workspace for a force call (allocating on first use or growth).
 template <typename T>
 static int handle_ws(aica_dil *h, ForceWs &ws, hipStream_t st) {
-  const int64_t n = h->n, ng = h->grp.ng, J = h->jtotal;
+  using V4 = typename Vec4<T>::type;
+  const bool full = full_lists(h, sizeof(T));
+  const int64_t n = h->n, ng = full ? h->nb.ng : h->grp.ng;
   int rc;
-  if ((rc = prepare_jpart(h, sizeof(T) * 4 * std::max<int64_t>(J, 1), st))) return rc;
-  if ((rc = h->d_own.ensure(sizeof(T) * 8 * std::max<int64_t>(n, 1)))) return rc;
+  if ((rc = h->d_pos.ensure(sizeof(V4) * std::max<int64_t>(n, 1)))) return rc;
+  if (full) {
+    if ((rc = h->d_box.ensure(sizeof(T) * 6 * std::max<int64_t>(ng, 1)))) return rc;
+  } else {
+    if ((rc = prepare_jpart(h, sizeof(T) * 4 * std::max<int64_t>(h->jtotal, 1), st))) return rc;
+    if ((rc = h->d_own.ensure(sizeof(T) * 8 * std::max<int64_t>(n, 1)))) return rc;
+  }
   if ((rc = h->d_gpart.ensure(sizeof(double) * 2 * std::max<int64_t>(ng, 1)))) return rc;
   if ((rc = h->d_gnp.ensure(16 * std::max<int64_t>(ng, 1)))) return rc;
   if ((rc = h->d_red.ensure(sizeof(double) * 8 * kRedBlocks))) return rc;
   ws.pos = h->d_pos.p;
+  ws.box = h->d_box.p;
   ws.own = h->d_own.p;
   ws.jpart = h->d_jpart.p;
   ws.gpart = h->d_gpart.p;
@@ -1574,11 +1776,13 @@ static int check_step(aica_dil *h, const void *pos_dev) {
   return AICA_OK;
 }
 
-// Pair kernel, finalize and reductions of a force call on the workspace ws (positions already gathered).
+// Gather, pair kernel, finalize and reductions of a force call on the workspace ws.
 template <typename T>
-static int forces_impl(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool comp, void *forces_dev, double *uw_dev,
-                       int64_t *npairs_dev, hipStream_t st, bool prof = true) {
-  const int64_t n = h->n, ng = h->grp.ng;
+static int forces_impl(aica_dil *h, const ForceWs &ws, const void *pos_dev, const int32_t *species, const LJTab &tab,
+                       bool comp, void *forces_dev, double *uw_dev, int64_t *npairs_dev, hipStream_t st,
+                       bool prof = true) {
+  const bool full = full_lists(h, sizeof(T));
+  const int64_t n = h->n, ng = full ? h->nb.ng : h->grp.ng;
   int rc;
   const bool was = h->profiling;
   h->profiling = was && prof;  // the timing events are created only where the call may allocate
@@ -1587,18 +1791,27 @@ static int forces_impl(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
     bool v;
     ~Restore() { h->profiling = v; }
   } restore{h, was};
+  rc = full ? gather_groups<T>(h, pos_dev, species, tab.nsp, st, ws.pos, ws.box)
+            : gather_to<T>(h, pos_dev, species, tab.nsp, st, ws.pos);
+  if (rc) return rc;
   {
     ProfScope ps(h, "pair_fwd", st);
-    if ((rc = launch_pair<T, 0>(h, ws, tab, comp, st, 0, nullptr))) return rc;
-    h->wsteps_valid = ws.gnp == h->d_gnp.p;  // the lane-pair diagnostic reads the handle's partials
+    if (full) {
+      if ((rc = launch_force<T>(h, ws, tab, comp, forces_dev, st))) return rc;
+    } else if constexpr (sizeof(T) == 4) {
+      if ((rc = launch_pair<T, 0>(h, ws, tab, comp, st, 0, nullptr))) return rc;
+    }
+    h->wsteps_groups = ws.gnp == h->d_gnp.p ? ng : 0;  // the lane-pair diagnostic reads the handle's partials
   }
   {
     ProfScope ps(h, "finalize", st);
-    if (n > 0 && forces_dev) {
-      if (comp && sizeof(T) == 4)
-        launch_finalize<T, true>(h, ws, forces_dev, st);
-      else
-        launch_finalize<T, false>(h, ws, forces_dev, st);
+    if constexpr (sizeof(T) == 4) {
+      if (!full && n > 0 && forces_dev) {
+        if (comp)
+          launch_finalize<T, true>(h, ws, forces_dev, st);
+        else
+          launch_finalize<T, false>(h, ws, forces_dev, st);
+      }
     }
     if (uw_dev || npairs_dev) {
       int64_t chunk;
@@ -1608,7 +1821,8 @@ static int forces_impl(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
                          2, 0, chunk, pu);
       hipLaunchKernelGGL((k_reduce_rows<1, unsigned long long>), dim3(nb), dim3(kRedThreads), 0, st,
                          (const unsigned long long *)ws.gnp, ng, 2, 0, chunk, pn);
-      hipLaunchKernelGGL(k_reduce_uw, dim3(1), dim3(kRedThreads), 0, st, pu, pn, nb, uw_dev, npairs_dev);
+      // with the full lists each pair is counted from both sides
+      hipLaunchKernelGGL(k_reduce_uw, dim3(1), dim3(kRedThreads), 0, st, pu, pn, nb, uw_dev, npairs_dev, full ? 2 : 1);
     }
     HIPCHK(hipGetLastError());
   }
@@ -1618,11 +1832,10 @@ static int forces_impl(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
 template <typename T>
 static int forces_alloc(aica_dil *h, const void *pos_dev, const int32_t *species, const LJTab &tab, bool comp,
                         void *forces_dev, double *uw_dev, int64_t *npairs_dev, hipStream_t st) {
-  int rc;
-  if ((rc = gather<T>(h, pos_dev, species, tab.nsp, st))) return rc;
   ForceWs ws;
-  if ((rc = handle_ws<T>(h, ws, st))) return rc;
-  return forces_impl<T>(h, ws, tab, comp, forces_dev, uw_dev, npairs_dev, st);
+  int rc = handle_ws<T>(h, ws, st);
+  if (rc) return rc;
+  return forces_impl<T>(h, ws, pos_dev, species, tab, comp, forces_dev, uw_dev, npairs_dev, st);
 }
 
 int aica_forces(aica_dil *h, const void *pos_dev, const int32_t *species_dev, const aica_params *params,
@@ -1665,14 +1878,16 @@ template <typename T>
 static int forces_noalloc(aica_dil *h, const void *pos_dev, const int32_t *species, const LJTab &tab, bool comp,
                           void *forces_dev, double *uw_dev, int64_t *npairs_dev, hipStream_t st) {
   using V4 = typename Vec4<T>::type;
-  const int64_t n = h->n, ng = h->grp.ng, J = h->jtotal;
+  const bool full = full_lists(h, sizeof(T));
+  const int64_t n = h->n, ng = full ? h->nb.ng : h->grp.ng, J = h->jtotal;
   const size_t b_pos = align256(sizeof(V4) * std::max<int64_t>(n, 1));
   const size_t b_own = align256(sizeof(T) * 8 * std::max<int64_t>(n, 1));
   const size_t b_jpart = align256(sizeof(T) * 4 * std::max<int64_t>(J, 1));
   const size_t b_gpart = align256(sizeof(double) * 2 * std::max<int64_t>(ng, 1));
   const size_t b_gnp = align256(16 * std::max<int64_t>(ng, 1));
   const size_t b_red = align256(sizeof(double) * 8 * kRedBlocks);
-  const size_t need = b_pos + b_own + b_jpart + b_gpart + b_gnp + b_red;
+  const size_t b_box = full ? align256(sizeof(T) * 6 * std::max<int64_t>(ng, 1)) : 0;
+  const size_t need = b_pos + b_box + b_own + b_jpart + b_gpart + b_gnp + b_red;
   if (need > kScratchBytes)
     return fail(AICA_E_INVAL, "aica_forces_noalloc needs " + std::to_string(need) + " bytes of scratch for " +
                                   std::to_string(n) + " molecules; the fixed scratch holds " +
@@ -1684,19 +1899,21 @@ static int forces_noalloc(aica_dil *h, const void *pos_dev, const int32_t *speci
   if (rc) return rc;
   ForceWs ws;
   ws.pos = base;
-  ws.own = base + b_pos;
-  ws.jpart = base + b_pos + b_own;
-  ws.gpart = base + b_pos + b_own + b_jpart;
-  ws.gnp = base + b_pos + b_own + b_jpart + b_gpart;
-  ws.red = base + b_pos + b_own + b_jpart + b_gpart + b_gnp;
-  // the array keeps the last call's records: every record's tag is cleared (a fill kernel, no memset node)
-  ws.epoch = 1;
-  const int64_t words = (int64_t)(sizeof(T) * 4 * std::max<int64_t>(J, 1) / 4);
-  hipLaunchKernelGGL((k_fill<uint32_t>), dim3(grid1d(words, 256)), dim3(256), 0, st, (uint32_t *)ws.jpart, words,
-                     0xFFFFFFFFu);
-  HIPCHK(hipGetLastError());
-  if ((rc = gather_to<T>(h, pos_dev, species, tab.nsp, st, ws.pos))) return rc;
-  return forces_impl<T>(h, ws, tab, comp, forces_dev, uw_dev, npairs_dev, st, false);
+  ws.box = base + b_pos;
+  ws.own = base + b_pos + b_box;
+  ws.jpart = base + b_pos + b_box + b_own;
+  ws.gpart = base + b_pos + b_box + b_own + b_jpart;
+  ws.gnp = base + b_pos + b_box + b_own + b_jpart + b_gpart;
+  ws.red = base + b_pos + b_box + b_own + b_jpart + b_gpart + b_gnp;
+  if (!full) {
+    // the array keeps the last call's records: every record's tag is cleared (a fill kernel, no memset node)
+    ws.epoch = 1;
+    const int64_t words = (int64_t)(sizeof(T) * 4 * std::max<int64_t>(J, 1) / 4);
+    hipLaunchKernelGGL((k_fill<uint32_t>), dim3(grid1d(words, 256)), dim3(256), 0, st, (uint32_t *)ws.jpart, words,
+                       0xFFFFFFFFu);
+    HIPCHK(hipGetLastError());
+  }
+  return forces_impl<T>(h, ws, pos_dev, species, tab, comp, forces_dev, uw_dev, npairs_dev, st, false);
 }
 
 int aica_forces_noalloc(aica_dil *h, const void *pos_dev, const int32_t *species_dev, const aica_params *params,
@@ -1856,10 +2073,9 @@ int aica_dil_info(const aica_dil *h, aica_info *info) {
 int aica_work_stats(const aica_dil *h, int64_t *dil_candidates, int64_t *lane_pairs) {
   if (!h) return fail(AICA_E_INVAL, "handle is NULL");
   if (!h->bin_valid) return fail(AICA_E_INVAL, "aica_bin must succeed first");
-  const int64_t nc = h->geo.nc, ng = h->grp.ng;
-  std::vector<int32_t> cs(nc + 1), gs(ng + 1);
+  const int64_t nc = h->geo.nc, ng = h->wsteps_groups;
+  std::vector<int32_t> cs(nc + 1);
   HIPCHK(hipMemcpy(cs.data(), h->d_cell_start.p, 4 * (nc + 1), hipMemcpyDeviceToHost));
-  HIPCHK(hipMemcpy(gs.data(), h->d_g_start.p, 4 * (ng + 1), hipMemcpyDeviceToHost));
   if (dil_candidates) {
     int64_t cand = 0;
     for (int64_t s = 0; s < nc; ++s) {
@@ -1871,7 +2087,7 @@ int aica_work_stats(const aica_dil *h, int64_t *dil_candidates, int64_t *lane_pa
   }
   if (lane_pairs) {
     // wave-steps counted by the last forward pair kernel, 64 lane-pair evaluations each
-    if (!h->wsteps_valid) return fail(AICA_E_INVAL, "aica_forces must run after aica_bin first");
+    if (ng == 0) return fail(AICA_E_INVAL, "aica_forces must run after aica_bin first");
     std::vector<unsigned long long> gn(2 * ng);
     HIPCHK(hipMemcpy(gn.data(), h->d_gnp.p, 16 * ng, hipMemcpyDeviceToHost));
     int64_t lp = 0;

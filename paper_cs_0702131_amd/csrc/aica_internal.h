@@ -136,4 +136,28 @@ struct Groups {
 int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
                  const std::vector<CellPair> &pairs, double density, double target, Groups &out);
 
+// A run of consecutive sorted cells [d0, d1) of one j-group, read through group-pair entry e.
+struct CellRun {
+  int32_t d0, d1, e, pad;
+};
+
+// Full neighbour lists of the interaction groups: every group lists all the cells its molecules can have a
+// partner in (both directions of every interacting cell pair), so that each molecule's sum is complete in
+// its own group.
+struct Neigh {
+  int64_t ng = 0;
+  std::vector<int32_t> cell0;    // [ng+1] first sorted cell of each group
+  std::vector<double> orig;      // [ng][3] group origin (multiple of 2^-15)
+  std::vector<int64_t> e_off;    // [ng+1] entries (j-group, image) of each group, without the group itself
+  std::vector<int32_t> e_B;      // j-group
+  std::vector<int8_t> e_code;    // image code 9 (n0 + 1) + 3 (n1 + 1) + (n2 + 1)
+  std::vector<int32_t> e_rev;    // the entry of j-group B that refers back (group A, image -n)
+  std::vector<int64_t> run_off;  // [ng+1]
+  std::vector<CellRun> runs;
+  double reach = 0;              // largest coordinate (any axis) of a listed molecule in a group's frame
+};
+
+int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
+                const std::vector<CellPair> &pairs, bool whole_groups, double density, double target, Neigh &out);
+
 }  // namespace aica

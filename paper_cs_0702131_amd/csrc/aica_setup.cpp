@@ -809,11 +809,10 @@ int build_cell_pairs(const Geometry &g, const std::vector<int32_t> &order, const
 
 // ------------------------------------------------------------------ interaction groups
 
-int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
-                 const std::vector<CellPair> &pairs, double density, double target, Groups &G) {
+static void cut_groups(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
+                       double density, double target, std::vector<int32_t> &cell0) {
   const int64_t nc = g.nc;
-  G.cell0.clear();
-  G.of_cell.assign(nc, 0);
+  cell0.clear();
   // Groups are subtrees of the k-d tree of the sorted order: descending from the root, a subtree whose
   // expected occupancy is at most the target becomes a group, so every group is a compact box-like block
   // of cells (a run of the sorted order cut at arbitrary places would straddle subtrees and spread out).
@@ -829,7 +828,7 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
     stack.pop_back();
     if (r.e <= r.b) continue;
     if (r.e - r.b == 1 || density * (vpre[r.e] - vpre[r.b]) <= target) {
-      G.cell0.push_back((int32_t)r.b);
+      cell0.push_back((int32_t)r.b);
       continue;
     }
     int64_t mid = r.b + 1;
@@ -838,6 +837,13 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
     stack.push_back({mid, r.e, r.depth + 1});
     stack.push_back({r.b, mid, r.depth + 1});
   }
+}
+
+int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
+                 const std::vector<CellPair> &pairs, double density, double target, Groups &G) {
+  const int64_t nc = g.nc;
+  G.of_cell.assign(nc, 0);
+  cut_groups(g, order, split_depth, density, target, G.cell0);
   for (size_t k = 0; k < G.cell0.size(); ++k) {
     const int64_t e = k + 1 < G.cell0.size() ? G.cell0[k + 1] : nc;
     for (int64_t s = G.cell0[k]; s < e; ++s) G.of_cell[s] = (int32_t)k;
@@ -970,6 +976,174 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
     G.nl_r[k] = (int32_t)(1 + cfill[d] - G.rc_off[d]);
     G.rc_e[cfill[d]++] = G.nl_e[k];
   }
+  return AICA_OK;
+}
+
+// Gaps of up to this many unlisted cells inside a run are read with it: the pair kernels test every molecule
+// against the group's box anyway, and fewer runs cost less to expand than a few more molecules to test.
+static constexpr int32_t kRunGap = 2;
+
+int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
+                const std::vector<CellPair> &pairs, bool whole_groups, double density, double target, Neigh &N) {
+  const int64_t nc = g.nc;
+  cut_groups(g, order, split_depth, density, target, N.cell0);
+  const int64_t ng = N.ng = (int64_t)N.cell0.size();
+  N.cell0.push_back((int32_t)nc);
+  std::vector<int32_t> of_cell(nc);
+  for (int64_t a = 0; a < ng; ++a)
+    for (int64_t s = N.cell0[a]; s < N.cell0[a + 1]; ++s) of_cell[s] = (int32_t)a;
+  // origins: mean of member centroids rounded to a multiple of 2^-15; reach: the group's box about its origin
+  N.orig.assign(3 * ng, 0.0);
+  std::vector<double> ext(ng);
+  parallel_for(ng, [&](int64_t b, int64_t e, int) {
+    for (int64_t a = b; a < e; ++a) {
+      double s[3] = {0, 0, 0};
+      for (int32_t sc = N.cell0[a]; sc < N.cell0[a + 1]; ++sc)
+        for (int q = 0; q < 3; ++q) s[q] += g.ccen[3 * (int64_t)order[sc] + q];
+      const double n = N.cell0[a + 1] - N.cell0[a];
+      for (int q = 0; q < 3; ++q) N.orig[3 * a + q] = std::ldexp(std::nearbyint(std::ldexp(s[q] / n, 15)), -15);
+      ext[a] = 0;
+      for (int32_t sc = N.cell0[a]; sc < N.cell0[a + 1]; ++sc)
+        for (int q = 0; q < 3; ++q) {
+          const int64_t c = order[sc];
+          ext[a] = std::max({ext[a], std::fabs(g.lo[3 * c + q] - N.orig[3 * a + q]), std::fabs(g.hi[3 * c + q] - N.orig[3 * a + q])});
+        }
+    }
+  });
+  std::vector<int64_t> pstart(ng + 1, 0);
+  {
+    int64_t p = 0;
+    for (int64_t a = 0; a < ng; ++a) {
+      pstart[a] = p;
+      while (p < (int64_t)pairs.size() && pairs[p].sc < N.cell0[a + 1]) ++p;
+    }
+    pstart[ng] = (int64_t)pairs.size();
+  }
+  // Listed cells of group A as keys (image code, sorted cell): from the pairs of A's own cells directly
+  // (fwd), and from the pairs whose other cell lies in A, collected by group (B, code, cell) and dealt to B.
+  struct Rev {
+    int32_t B, cell;
+    int8_t code;
+  };
+  auto key_of = [](int code, int64_t cell) { return ((int64_t)code << 40) | cell; };
+  std::vector<std::vector<int64_t>> lists(ng);
+  std::vector<std::vector<Rev>> rev(ng);
+  parallel_for(ng, [&](int64_t b, int64_t e, int) {
+    std::vector<int64_t> L;
+    std::vector<Rev> R;
+    for (int64_t a = b; a < e; ++a) {
+      L.clear();
+      R.clear();
+      for (int64_t p = pstart[a]; p < pstart[a + 1]; ++p) {
+        const CellPair &cp = pairs[p];
+        const int32_t B = of_cell[cp.sd];
+        const int code = img_code(cp.img[0], cp.img[1], cp.img[2]);
+        if (B == a && code == 13) continue;
+        L.push_back(key_of(code, cp.sd));
+        const Rev r{B, cp.sc, (int8_t)(26 - code)};
+        if (R.empty() || R.back().B != r.B || R.back().cell != r.cell || R.back().code != r.code) R.push_back(r);
+      }
+      std::sort(L.begin(), L.end());
+      L.erase(std::unique(L.begin(), L.end()), L.end());
+      lists[a] = L;
+      rev[a] = R;
+    }
+  });
+  {
+    std::vector<int64_t> roff(ng + 1, 0);
+    for (int64_t a = 0; a < ng; ++a)
+      for (const Rev &r : rev[a]) roff[r.B + 1]++;
+    for (int64_t a = 0; a < ng; ++a) roff[a + 1] += roff[a];
+    std::vector<int64_t> rk(roff[ng]), fill(roff.begin(), roff.end() - 1);
+    for (int64_t a = 0; a < ng; ++a) {
+      for (const Rev &r : rev[a]) rk[fill[r.B]++] = key_of(r.code, r.cell);
+      std::vector<Rev>().swap(rev[a]);
+    }
+    parallel_for(ng, [&](int64_t b, int64_t e, int) {
+      for (int64_t a = b; a < e; ++a) {
+        std::vector<int64_t> &L = lists[a];
+        L.insert(L.end(), rk.begin() + roff[a], rk.begin() + roff[a + 1]);
+        std::sort(L.begin(), L.end());
+        L.erase(std::unique(L.begin(), L.end()), L.end());
+      }
+    });
+  }
+  // entries (code, B) and runs of cells: the keys are sorted by (code, cell), so by (code, B, cell)
+  std::vector<std::vector<int64_t>> ents(ng);
+  std::vector<std::vector<CellRun>> runs(ng);
+  parallel_for(ng, [&](int64_t b, int64_t e, int) {
+    for (int64_t a = b; a < e; ++a) {
+      std::vector<int64_t> &E = ents[a];
+      std::vector<CellRun> &R = runs[a];
+      for (const int64_t key : lists[a]) {
+        const int32_t d = (int32_t)(key & 0x7FFFFFFF);
+        const int64_t ek = ((key >> 40) << 32) | of_cell[d];
+        if (E.empty() || E.back() != ek) {
+          E.push_back(ek);
+          R.push_back(CellRun{d, d + 1, (int32_t)E.size() - 1, 0});
+        } else if (d - R.back().d1 <= kRunGap) {
+          R.back().d1 = d + 1;
+        } else {
+          R.push_back(CellRun{d, d + 1, (int32_t)E.size() - 1, 0});
+        }
+      }
+      if (whole_groups) {
+        // The vertex predicate does not list every cell pair in range, so a cell that one group reads need not
+        // have the other side's cells read back: whole groups are read instead, which is symmetric.
+        R.clear();
+        for (size_t k = 0; k < E.size(); ++k) {
+          const int32_t B = (int32_t)(E[k] & 0x7FFFFFFF);
+          R.push_back(CellRun{N.cell0[B], N.cell0[B + 1], (int32_t)k, 0});
+        }
+      }
+      std::vector<int64_t>().swap(lists[a]);
+    }
+  });
+  N.e_off.assign(ng + 1, 0);
+  N.run_off.assign(ng + 1, 0);
+  for (int64_t a = 0; a < ng; ++a) {
+    N.e_off[a + 1] = N.e_off[a] + (int64_t)ents[a].size();
+    N.run_off[a + 1] = N.run_off[a] + (int64_t)runs[a].size();
+  }
+  const int64_t E = N.e_off[ng];
+  if (E >= (1LL << 31)) return fail(AICA_E_NOMEM, "too many group pairs");
+  N.e_B.resize(E);
+  N.e_code.resize(E);
+  N.e_rev.resize(E);
+  N.runs.resize(N.run_off[ng]);
+  parallel_for(ng, [&](int64_t b, int64_t e, int) {
+    for (int64_t a = b; a < e; ++a) {
+      int64_t k = N.e_off[a];
+      for (const int64_t ek : ents[a]) {
+        const int32_t B = (int32_t)(ek & 0x7FFFFFFF);
+        const int code = (int)(ek >> 32);
+        N.e_B[k] = B;
+        N.e_code[k] = (int8_t)code;
+        const int64_t back = ((int64_t)(26 - code) << 32) | a;
+        N.e_rev[k] = (int32_t)(N.e_off[B] + (std::lower_bound(ents[B].begin(), ents[B].end(), back) - ents[B].begin()));
+        ++k;
+      }
+      CellRun *o = N.runs.data() + N.run_off[a];
+      for (CellRun r : runs[a]) {
+        r.e += (int32_t)N.e_off[a];
+        *o++ = r;
+      }
+    }
+  });
+  double reach = 0;
+  for (int64_t a = 0; a < ng; ++a) {
+    reach = std::max(reach, ext[a]);
+    for (int64_t k = N.e_off[a]; k < N.e_off[a + 1]; ++k) {
+      const int code = N.e_code[k];
+      const Xf T = image_transform(g, code / 9 - 1, (code / 3) % 3 - 1, code % 3 - 1);
+      double tb[3];
+      T.apply(&N.orig[3 * (int64_t)N.e_B[k]], tb);
+      double m = 0;
+      for (int q = 0; q < 3; ++q) m = std::max(m, std::fabs(tb[q] - N.orig[3 * a + q]));
+      reach = std::max(reach, m + ext[N.e_B[k]] * (T.rot ? std::sqrt(3.0) : 1.0));
+    }
+  }
+  N.reach = reach;
   return AICA_OK;
 }
 
