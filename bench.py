@@ -57,7 +57,7 @@ def workload(name):
 
 
 # Kernel sources whose digest ties the traffic counters to the code they were measured on.
-KERNEL_SOURCES = ["aica_pair.inc", "aica_adjoint_pair.inc", "aica_device.hip", "aica_kernels.h", "aica_adjoint.inc"]
+KERNEL_SOURCES = ["aica_pair.inc", "aica_neigh.inc", "aica_device.hip", "aica_kernels.h", "aica_adjoint.inc"]
 
 
 def kernel_digest():
@@ -95,7 +95,7 @@ def measured_counters(kernel, workload):
     return out if digest == kernel_digest() else {}
 
 
-PAIR_KERNELS = {"pair_fwd": "k_pair<float, 0, 0, true, false>", "pair_adj": "k_pair_adj<float, 0, false>"}
+PAIR_KERNELS = {"pair_fwd": "k_force<float, 0, true, false>", "pair_adj": "k_force_adj<float, 0, false>"}
 TIMERS = ("pair_fwd", "pair_adj", "bin", "finalize", "finalize_adj")
 
 

@@ -752,7 +752,8 @@ __global__ __launch_bounds__(256) void k_gather_groups(const PT *__restrict__ po
                                                        const int32_t *__restrict__ cell_start,
                                                        const int32_t *__restrict__ cell0, const double *__restrict__ orig,
                                                        int64_t ng, int nsp, typename Vec4<T>::type *__restrict__ out,
-                                                       T *__restrict__ box) {
+                                                       T *__restrict__ box, const T *__restrict__ G,
+                                                       typename Vec4<T>::type *__restrict__ gout) {
   const int lane = threadIdx.x & 63;
   const int64_t a = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (a >= ng) return;
@@ -778,6 +779,13 @@ __global__ __launch_bounds__(256) void k_gather_groups(const PT *__restrict__ po
     else
       v.w = __builtin_bit_cast(double, (int64_t)t);
     out[m] = v;
+    if (G) {  // the adjoint's upstream gradient
+      v.x = G[3 * id];
+      v.y = G[3 * id + 1];
+      v.z = G[3 * id + 2];
+      v.w = (T)0;
+      gout[m] = v;
+    }
   }
 #pragma unroll
   for (int s = 1; s < 64; s <<= 1)
@@ -901,7 +909,6 @@ __device__ __forceinline__ T far_j() { return (T)-1e15; }
 
 #include "aica_pair.inc"
 #include "aica_neigh.inc"
-#include "aica_adjoint_pair.inc"
 
 namespace {
 
@@ -1615,12 +1622,8 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
   return AICA_OK;
 }
 
-// The force kernel: one block per group of the full neighbour lists.
 template <typename T>
-static int launch_force(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool comp, void *out, hipStream_t st) {
-  using V4 = typename Vec4<T>::type;
-  const int64_t ng = h->nb.ng, padded = ((ng + 7) / 8) * 8;
-  const bool rot = h->geo.has_rot;
+static NbLists nb_lists(const aica_dil *h) {
   NbLists nl;
   nl.cell0 = h->d_nb_cell0.as<int32_t>();
   nl.run_off = h->d_nb_run_off.as<int64_t>();
@@ -1630,8 +1633,18 @@ static int launch_force(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool c
   nl.e_rev = h->d_nb_erev.as<int32_t>();
   nl.e_vec = sizeof(T) == 4 ? h->d_nb_vec32.p : h->d_nb_vec64.p;
   nl.e_vec64 = h->d_nb_vec64.as<double4>();
-  nl.rot = rot ? h->d_rot64.as<double>() : nullptr;
-  nl.ng = ng;
+  nl.rot = h->geo.has_rot ? h->d_rot64.as<double>() : nullptr;
+  nl.ng = h->nb.ng;
+  return nl;
+}
+
+// The force kernel: one block per group of the full neighbour lists.
+template <typename T>
+static int launch_force(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool comp, void *out, hipStream_t st) {
+  using V4 = typename Vec4<T>::type;
+  const int64_t ng = h->nb.ng, padded = ((ng + 7) / 8) * 8;
+  const bool rot = h->geo.has_rot;
+  const NbLists nl = nb_lists<T>(h);
 #define AICA_FORCE(MIX, COMP, ROT)                                                                                  \
   hipLaunchKernelGGL((k_force<T, MIX, COMP, ROT>), dim3((unsigned)padded), dim3(kNbThreads), 0, st, nl,             \
                      (const V4 *)ws.pos, (const T *)ws.box, h->d_cell_start.as<int32_t>(), h->d_perm.as<int32_t>(),  \
@@ -1659,24 +1672,17 @@ static int launch_force(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool c
   return AICA_OK;
 }
 
-// The adjoint pair kernel (one, two, or three to eight species).
+// The adjoint kernel (one, two, or three to eight species), on the groups of the full lists.
 template <typename T>
-static int launch_adj(aica_dil *h, const LJTab &tab, const AdjTab &at, hipStream_t st) {
+static int launch_adj(aica_dil *h, const LJTab &tab, const AdjTab &at, void *out, hipStream_t st) {
   using V4 = typename Vec4<T>::type;
-  const int64_t ng = h->grp.ng;
-  constexpr int NW = adj_waves(sizeof(T));
-  const int64_t nblocks = (ng + NW - 1) / NW;
-  const int64_t padded = ((nblocks + 7) / 8) * 8;
-  const V4 *ev = sizeof(T) == 4 ? (const V4 *)h->d_e_vec32.p : (const V4 *)h->d_e_vec64.p;
-  const double *rot = h->geo.has_rot ? h->d_rot64.as<double>() : nullptr;
-  const double4 *evd = h->geo.has_rot ? h->d_e_vec64.as<double4>() : nullptr;
-#define AICA_LAUNCH_ADJ(MIX, ROT)                                                                                   \
-  hipLaunchKernelGGL((k_pair_adj<T, MIX, ROT>), dim3((unsigned)padded), dim3(64 * NW), 0, st, h->d_pos.as<V4>(),   \
-                     h->d_gG.as<V4>(), h->d_g_start.as<int32_t>(), h->d_g_cell0.as<int32_t>(),                     \
-                     h->d_cell_start.as<int32_t>(), ev, h->d_slot_base.as<int64_t>(), h->d_nl_off.as<int64_t>(),    \
-                     h->d_nl_e.as<int32_t>(), h->d_nl_d.as<int32_t>(), h->d_nl_r.as<int32_t>(), h->d_jpart.as<double>(), \
-                     h->d_own.as<T>(), h->d_gpar.as<double>(), ng, padded, tab, at, rot, evd, h->epoch)
-  if (rot) {
+  const int64_t ng = h->nb.ng, padded = ((ng + 7) / 8) * 8;
+  const NbLists nl = nb_lists<T>(h);
+#define AICA_LAUNCH_ADJ(MIX, ROT)                                                                                    \
+  hipLaunchKernelGGL((k_force_adj<T, MIX, ROT>), dim3((unsigned)padded), dim3(kNbThreads), 0, st, nl,                \
+                     h->d_pos.as<V4>(), h->d_gG.as<V4>(), h->d_box.as<T>(), h->d_cell_start.as<int32_t>(),           \
+                     h->d_perm.as<int32_t>(), padded, tab, at, (T *)out, h->d_gpar.as<double>())
+  if (h->geo.has_rot) {
     if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, true);
     else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, true);
     else AICA_LAUNCH_ADJ(2, true);
@@ -1727,13 +1733,13 @@ static int gather(aica_dil *h, const void *pos_dev, const int32_t *species, int 
 // Gather the binned positions by the groups of the full lists into pos, and their boxes into box.
 template <typename T>
 static int gather_groups(aica_dil *h, const void *pos_dev, const int32_t *species, int nsp, hipStream_t st, void *pos,
-                         void *box) {
+                         void *box, const void *G = nullptr, void *gsort = nullptr) {
   using V4 = typename Vec4<T>::type;
   const int64_t ng = h->nb.ng;
 #define AICA_GATHER(PT)                                                                                               \
   hipLaunchKernelGGL((k_gather_groups<T, PT>), dim3(grid1d(ng, 4)), dim3(256), 0, st, (const PT *)pos_dev, species,   \
                      h->d_perm.as<int32_t>(), h->d_cell_start.as<int32_t>(), h->d_nb_cell0.as<int32_t>(),             \
-                     h->d_nb_orig.as<double>(), ng, nsp, (V4 *)pos, (T *)box)
+                     h->d_nb_orig.as<double>(), ng, nsp, (V4 *)pos, (T *)box, (const T *)G, (V4 *)gsort)
   if (h->bin_dtype == AICA_FP64) AICA_GATHER(double);
   else AICA_GATHER(float);
 #undef AICA_GATHER

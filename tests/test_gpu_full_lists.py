@@ -80,3 +80,48 @@ def test_fp32_on_either_side_of_the_list_choice(A, n):
     rms = out["fp64"][0].pow(2).sum(1).mean().sqrt()
     assert ((out["fp32"][0] - out["fp64"][0]).pow(2).sum(1).sqrt().max() / rms).item() < 1e-5
     assert np.all(np.abs(out["fp32"][1] - out["fp64"][1]) <= 1e-5 * np.abs(out["fp64"][1]))
+
+
+@pytest.mark.parametrize("n,L,cells,nsp", [(1, 6.0, 1, 1), (33, 4.0, 1, 2), (129, 5.5, 1, 1), (1025, 11.0, 1, 3), (2500, 14.0, 1, 1)])
+def test_adjoint_edges(A, oracle, n, L, cells, nsp):
+    """The full-list adjoint at the same edges, both precisions (bars: FP64 1e-12, FP32 1e-6 of the rms over rows
+    and of the parameter gradients)."""
+    import torch
+    L = float(W.qround(L))
+    nodes = W.uniform_nodes(L, cells)
+    mesh = W.hex_mesh(nodes, nodes, nodes)
+    x = _lattice(L, n, 91 + n)
+    rng = np.random.default_rng(5)
+    G = W.qround(rng.standard_normal((n, 3)))
+    sp = rng.integers(0, nsp, n).astype(np.int32)
+    eps, sig = np.array([1.0, 0.6, 0.8])[:nsp], np.array([1.0, 0.9, 0.95])[:nsp]
+    print(f"adjoint edges: n={n} L={L} species={nsp}", flush=True)
+    rx, re, rs, _ = oracle.adjoint(x, sp, eps, sig, 2.5, mesh.periodic, G, 0.1)
+    d = A.DIL(mesh, 2.5)
+    for prec, dt, tol in (("fp64", torch.float64, 1e-12), ("fp32", torch.float32, 1e-6)):
+        t = torch.tensor(x, dtype=dt, device="cuda")
+        A.aica_bin(d, t)
+        gx, ge, gs = A.aica_forces_adjoint(d, t, torch.tensor(G, dtype=dt, device="cuda"), 0.1,
+                                           torch.tensor(sp, device="cuda"), eps, sig, precision=prec)
+        rms = max(np.sqrt((rx ** 2).mean()), 1e-30)
+        assert np.abs(gx.double().cpu().numpy() - rx).max() <= tol * rms
+        assert np.abs(ge.cpu().numpy() - re).max() <= tol * max(np.abs(re).max(), 1e-30)
+        assert np.abs(gs.cpu().numpy() - rs).max() <= tol * max(np.abs(rs).max(), 1e-30)
+
+
+def test_adjoint_keeps_a_nan_gradient_in_reach(A):
+    """A molecule whose upstream gradient is NaN reaches the rows of its partners inside the cut-off and no others."""
+    import torch
+    L, n = float(W.qround(12.0)), 900
+    nodes = W.uniform_nodes(L, 5)
+    mesh = W.hex_mesh(nodes, nodes, nodes)
+    x = _lattice(L, n, 13)
+    G = W.qround(np.random.default_rng(6).standard_normal((n, 3)))
+    G[0] = np.nan
+    d = A.DIL(mesh, 2.5)
+    near = ((x - x[0]) ** 2).sum(1) < 2.5 ** 2
+    for prec, dt in (("fp64", torch.float64), ("fp32", torch.float32)):
+        t = torch.tensor(x, dtype=dt, device="cuda")
+        A.aica_bin(d, t)
+        gx, _, _ = A.aica_forces_adjoint(d, t, torch.tensor(G, dtype=dt, device="cuda"), 0.1, precision=prec)
+        assert np.array_equal(np.isnan(gx.cpu().numpy()).any(1), near)
