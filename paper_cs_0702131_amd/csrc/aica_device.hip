@@ -657,30 +657,30 @@ __global__ void k_scan_add(OutT *out, int64_t n, const OutT *tile_sum) {
   if (i < n) out[i] += tile_sum[i / kScanTile];
 }
 
-// rank_t[t]: the place the locate kernels' count took for the molecule inside its cell (any order; the
-// cells are sorted by molecule id next).
+// rank_t[t]: the place the locate kernels' count took for the molecule inside its cell (any order; the cells are
+// sorted by molecule id next).  raw: the molecules by cell; cell_of: their cells.
 __global__ void k_scatter(const int32_t *cell_t, const int32_t *trav, int64_t n, const int32_t *cell_start,
-                          const int32_t *rank_t, int32_t *perm) {
+                          const int32_t *rank_t, int32_t *raw, int32_t *cell_of) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n) return;
   const int32_t c = cell_t[t];
-  if (c >= 0) perm[cell_start[c] + rank_t[t]] = trav ? trav[t] : (int32_t)t;  // c < 0: unlocated (an error)
+  if (c < 0) return;  // unlocated (an error)
+  const int32_t m = cell_start[c] + rank_t[t];
+  raw[m] = trav ? trav[t] : (int32_t)t;
+  cell_of[m] = c;
 }
 
-// Ascending molecule id inside every cell (the scatter's atomics leave an arbitrary order).
-__global__ void k_sort_cells(const int32_t *cell_start, int64_t nc, int32_t *perm) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= nc) return;
-  const int32_t b = cell_start[c], e = cell_start[c + 1];
-  for (int32_t i = b + 1; i < e; ++i) {
-    const int32_t v = perm[i];
-    int32_t j = i - 1;
-    while (j >= b && perm[j] > v) {
-      perm[j + 1] = perm[j];
-      --j;
-    }
-    perm[j + 1] = v;
-  }
+// Ascending molecule id inside every cell (the locate kernels' counters leave an arbitrary order): every molecule
+// counts the smaller ids of its cell.  One thread per molecule: an insertion sort with a thread per cell took
+// 1.67 ms on 60,001 molecules in cells of a hundred.
+__global__ void k_sort_cells(const int32_t *__restrict__ cell_start, const int32_t *__restrict__ cell_of,
+                             const int32_t *__restrict__ raw, int64_t nc, int64_t n, int32_t *__restrict__ perm) {
+  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (m >= n || m >= cell_start[nc]) return;  // fewer slots than n when some molecule is unlocated
+  const int32_t c = cell_of[m], b = cell_start[c], e = cell_start[c + 1], v = raw[m];
+  int32_t r = b;
+  for (int32_t k = b; k < e; ++k) r += raw[k] < v;
+  perm[r] = v;
 }
 
 __global__ void k_group_ranges(const int32_t *cell_start, const int32_t *g_cell0, int64_t ng, int32_t *g_start,
@@ -1469,17 +1469,18 @@ int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, voi
   // the unlocated count is read with the other counts below (one synchronisation per binning); an
   // unlocated molecule is left out of the occupancy and of the permutation
   if ((rc = scan_exclusive<int32_t>(h, h->d_count.as<int32_t>(), nc, h->d_cell_start.as<int32_t>(), st))) return rc;
-  if (n > 0)
+  if (n > 0) {
+    // the slow list is done with: its space takes the unsorted molecules
     hipLaunchKernelGGL(k_scatter, dim3(grid1d(n, 256)), dim3(256), 0, st, h->d_cell_of.as<int32_t>(), trav, n,
-                       h->d_cell_start.as<int32_t>(), h->d_rank.as<int32_t>(), h->d_perm.as<int32_t>());
-  hipLaunchKernelGGL(k_sort_cells, dim3(grid1d(nc, 256)), dim3(256), 0, st, h->d_cell_start.as<int32_t>(), nc,
-                     h->d_perm.as<int32_t>());
+                       h->d_cell_start.as<int32_t>(), h->d_rank.as<int32_t>(), h->d_slow.as<int32_t>(),
+                       h->d_cell_sorted.as<int32_t>());
+    hipLaunchKernelGGL(k_sort_cells, dim3(grid1d(n, 256)), dim3(256), 0, st, h->d_cell_start.as<int32_t>(),
+                       h->d_cell_sorted.as<int32_t>(), h->d_slow.as<int32_t>(), nc, n, h->d_perm.as<int32_t>());
+  }
   hipLaunchKernelGGL(k_group_ranges, dim3(grid1d(ng + 1, 256)), dim3(256), 0, st, h->d_cell_start.as<int32_t>(),
                      h->d_g_cell0.as<int32_t>(), ng, h->d_g_start.as<int32_t>(), h->d_mol_group.as<int32_t>());
   hipLaunchKernelGGL(k_slot_counts, dim3(grid1d(nc, 256)), dim3(256), 0, st, h->d_count.as<int32_t>(),
                      h->d_rcnt.as<int32_t>(), nc, h->d_jcnt.as<int32_t>());
-  hipLaunchKernelGGL(k_cell_of_sorted, dim3(grid1d(nc, 256)), dim3(256), 0, st, h->d_cell_start.as<int32_t>(), nc,
-                     h->d_cell_sorted.as<int32_t>());
   HIPCHK(hipGetLastError());
   if ((rc = scan_exclusive<int64_t>(h, h->d_jcnt.as<int32_t>(), nc, h->d_slot_base.as<int64_t>(), st))) return rc;
   int64_t jt = 0;
