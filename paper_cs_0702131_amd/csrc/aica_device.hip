@@ -912,80 +912,81 @@ __device__ __forceinline__ T far_j() { return (T)-1e15; }
 
 namespace {
 
-// Deterministic two-stage reduction of per-group partials.  Stage 1: block b sums the fixed row range
-// [b * chunk, (b + 1) * chunk) of a row-major [ng][stride] array (columns col0 .. col0 + K - 1, doubles or
-// unsigned integers read as doubles; integer sums stay exact below 2^53) in a fixed thread order and
-// tree.  Stage 2 (one block) sums the stage-1 rows in block order.
+// Deterministic reductions of per-group partials (rows of doubles, or of unsigned integers read as doubles: integer
+// sums stay exact below 2^53), always in a fixed order.  Up to kRedDirect rows one block sums them at once; more
+// rows go through stage-1 rows, one per block over a fixed range, which the last block's kernel sums in block order.
+// Each launch costs about 5 us here whatever it does, so the rows of several arrays share one.
 constexpr int kRedBlocks = 512, kRedThreads = 256;
+constexpr int64_t kRedDirect = 4096;
 
-template <int K, typename S>
-__global__ __launch_bounds__(kRedThreads) void k_reduce_rows(const S *in, int64_t ng, int stride, int col0,
-                                                              int64_t chunk, double *part) {
-  __shared__ double sh[K][kRedThreads];
+// Column sums of rows r0 .. r1 - 1 by the whole block, in out[K] of every thread.
+template <int K, typename F>
+__device__ void block_sum_rows(int64_t r0, int64_t r1, double *out, F row) {
+  __shared__ double sh[kRedThreads / 64][K];
   double acc[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) acc[k] = 0;
-  const int64_t r0 = (int64_t)blockIdx.x * chunk, r1 = std::min<int64_t>(ng, r0 + chunk);
-  for (int64_t r = r0 + threadIdx.x; r < r1; r += kRedThreads)
+  for (int64_t r = r0 + threadIdx.x; r < r1; r += kRedThreads) {
+    double v[K];
+    row(r, v);
 #pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] += (double)in[(int64_t)stride * r + col0 + k];
-#pragma unroll
-  for (int k = 0; k < K; ++k) sh[k][threadIdx.x] = acc[k];
-  __syncthreads();
-  for (int o = kRedThreads / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o)
-#pragma unroll
-      for (int k = 0; k < K; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + o];
-    __syncthreads();
+    for (int k = 0; k < K; ++k) acc[k] += v[k];
   }
-  if (threadIdx.x == 0)
 #pragma unroll
-    for (int k = 0; k < K; ++k) part[(int64_t)K * blockIdx.x + k] = sh[k][0];
+  for (int o = 1; o < 64; o <<= 1)
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc[k] += __shfl_xor(acc[k], o, 64);
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < K; ++k) sh[threadIdx.x >> 6][k] = acc[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    out[k] = sh[0][k];
+    for (int w = 1; w < kRedThreads / 64; ++w) out[k] += sh[w][k];
+  }
 }
 
-// Stage 2 helper: thread 0 ends with the column sums of part[nb][K] in out[K].
-template <int K>
-__device__ void reduce_part_rows(const double *part, int nb, double *out) {
-  __shared__ double sh[K][kRedThreads];
-  double acc[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) acc[k] = 0;
-  for (int b = threadIdx.x; b < nb; b += kRedThreads)
-#pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] += part[(int64_t)K * b + k];
-#pragma unroll
-  for (int k = 0; k < K; ++k) sh[k][threadIdx.x] = acc[k];
-  __syncthreads();
-  for (int o = kRedThreads / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o)
-#pragma unroll
-      for (int k = 0; k < K; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int k = 0; k < K; ++k) out[k] = sh[k][0];
+// U, W and the pair count: rows (U, W) of gpart and the first column of gnp.
+__device__ __forceinline__ void uw_row(const double *gpart, const unsigned long long *gnp, int64_t r, double *v) {
+  v[0] = gpart[2 * r];
+  v[1] = gpart[2 * r + 1];
+  v[2] = (double)gnp[2 * r];
 }
-
-// U, W (FP64) and the pair count from the stage-1 rows (U, W) and (npairs).
-__global__ __launch_bounds__(kRedThreads) void k_reduce_uw(const double *part_uw, const double *part_np, int nb,
-                                                            double *uw, int64_t *npairs, int sides) {
-  double a[2], c[1];
-  reduce_part_rows<2>(part_uw, nb, a);
-  __syncthreads();
-  reduce_part_rows<1>(part_np, nb, c);
+__global__ __launch_bounds__(kRedThreads) void k_reduce_uw_rows(const double *gpart, const unsigned long long *gnp,
+                                                                 int64_t ng, int64_t chunk, double *part) {
+  double v[3];
+  block_sum_rows<3>(blockIdx.x * chunk, std::min<int64_t>(ng, (blockIdx.x + 1) * chunk), v,
+                    [&](int64_t r, double *x) { uw_row(gpart, gnp, r, x); });
+  if (threadIdx.x < 3) part[3 * (int64_t)blockIdx.x + threadIdx.x] = v[threadIdx.x];
+}
+// sides: how often each pair was counted.
+__global__ __launch_bounds__(kRedThreads) void k_reduce_uw(const double *gpart, const unsigned long long *gnp, int64_t ng,
+                                                            const double *part, int nb, double *uw, int64_t *npairs,
+                                                            int sides) {
+  double v[3];
+  if (nb > 0)
+    block_sum_rows<3>(0, nb, v, [&](int64_t r, double *x) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) x[k] = part[3 * r + k];
+    });
+  else
+    block_sum_rows<3>(0, ng, v, [&](int64_t r, double *x) { uw_row(gpart, gnp, r, x); });
   if (threadIdx.x == 0) {
     if (uw) {
-      uw[0] = a[0];
-      uw[1] = a[1];
+      uw[0] = v[0];
+      uw[1] = v[1];
     }
-    if (npairs) npairs[0] = (int64_t)c[0] / sides;
+    if (npairs) npairs[0] = (int64_t)v[2] / sides;
   }
 }
 
+// Stage-1 blocks (0: the rows are few enough for one block) and the rows of each.
 inline int red_blocks(int64_t ng, int64_t &chunk) {
-  const int nb = (int)std::min<int64_t>(kRedBlocks, std::max<int64_t>(1, (ng + kRedThreads - 1) / kRedThreads));
-  chunk = (std::max<int64_t>(ng, 1) + nb - 1) / nb;
+  chunk = ng;
+  if (ng <= kRedDirect) return 0;
+  const int nb = (int)std::min<int64_t>(kRedBlocks, (ng + kRedThreads - 1) / kRedThreads);
+  chunk = (ng + nb - 1) / nb;
   return nb;
 }
 
@@ -1823,13 +1824,13 @@ static int forces_impl(aica_dil *h, const ForceWs &ws, const void *pos_dev, cons
     if (uw_dev || npairs_dev) {
       int64_t chunk;
       const int nb = red_blocks(ng, chunk);
-      double *pu = (double *)ws.red, *pn = pu + 2 * kRedBlocks;
-      hipLaunchKernelGGL((k_reduce_rows<2, double>), dim3(nb), dim3(kRedThreads), 0, st, (const double *)ws.gpart, ng,
-                         2, 0, chunk, pu);
-      hipLaunchKernelGGL((k_reduce_rows<1, unsigned long long>), dim3(nb), dim3(kRedThreads), 0, st,
-                         (const unsigned long long *)ws.gnp, ng, 2, 0, chunk, pn);
+      const double *gp = (const double *)ws.gpart;
+      const unsigned long long *gn = (const unsigned long long *)ws.gnp;
+      if (nb > 0)
+        hipLaunchKernelGGL(k_reduce_uw_rows, dim3(nb), dim3(kRedThreads), 0, st, gp, gn, ng, chunk, (double *)ws.red);
       // with the full lists each pair is counted from both sides
-      hipLaunchKernelGGL(k_reduce_uw, dim3(1), dim3(kRedThreads), 0, st, pu, pn, nb, uw_dev, npairs_dev, full ? 2 : 1);
+      hipLaunchKernelGGL(k_reduce_uw, dim3(1), dim3(kRedThreads), 0, st, gp, gn, ng, (const double *)ws.red, nb, uw_dev,
+                         npairs_dev, full ? 2 : 1);
     }
     HIPCHK(hipGetLastError());
   }
