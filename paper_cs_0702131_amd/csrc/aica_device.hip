@@ -1578,6 +1578,12 @@ static int prepare_jpart(aica_dil *h, size_t bytes, hipStream_t st) {
   return AICA_OK;
 }
 
+// A block of four waves per group up to this many groups, a wave per group beyond: a small system has fewer groups than
+// the chip has SIMDs (1024), so a group's own length is what the call takes.  Pair kernel, FP32, one wave against a
+// block per group: 16 groups 66 and 40 us, 256 groups 80 and 44, 629 groups 70 and 43, 616 groups of two passes 267
+// and 228, 2048 groups 9 us less; 7963 groups 256 and 362 (every wave expands and prunes the whole j-side).
+constexpr int64_t kSplitGroups = 3072;
+
 // The half-list pair kernel: FP32 forces (MODE 0), pair export and per-molecule counts (MODE 1).
 template <typename T, int MODE>
 static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool comp, hipStream_t st, int64_t cap,
@@ -1585,7 +1591,9 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
   using V4 = typename Vec4<T>::type;
   const int64_t ng = h->grp.ng;
   constexpr int NW = pair_waves(sizeof(T));
-  const int64_t nblocks = (ng + NW - 1) / NW;
+  // few groups: a whole block per group
+  const bool split = MODE == 0 && ng <= kSplitGroups;
+  const int64_t nblocks = split ? ng : (ng + NW - 1) / NW;
   const int64_t padded = ((nblocks + 7) / 8) * 8;
   const V4 *pos = (const V4 *)ws.pos;
   const V4 *ev = sizeof(T) == 4 ? (const V4 *)h->d_e_vec32.p : (const V4 *)h->d_e_vec64.p;
@@ -1598,12 +1606,21 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
   const double *rot = h->geo.has_rot ? h->d_rot64.as<double>() : nullptr;
   const double4 *evd = h->geo.has_rot ? h->d_e_vec64.as<double4>() : nullptr;
   const int nsp = tab.nsp;
-#define AICA_LAUNCH_R(MIX, COMP, ROT)                                                                              \
-  hipLaunchKernelGGL((k_pair<T, MIX, MODE, COMP, ROT>), dim3((unsigned)padded), dim3(64 * NW), 0, st, pos,         \
+#define AICA_LAUNCH_S(MIX, COMP, ROT, SPLIT)                                                                       \
+  hipLaunchKernelGGL((k_pair<T, MIX, MODE, COMP, ROT, SPLIT>), dim3((unsigned)padded), dim3(64 * NW), 0, st, pos,         \
                      h->d_g_start.as<int32_t>(), h->d_g_cell0.as<int32_t>(), h->d_cell_start.as<int32_t>(), ev,    \
                      h->d_slot_base.as<int64_t>(), h->d_nl_off.as<int64_t>(), h->d_nl_e.as<int32_t>(),            \
                      h->d_nl_d.as<int32_t>(), h->d_nl_r.as<int32_t>(), jpart, own, gpart, gnp, ng, padded, tab,     \
                      rot, evd, h->d_perm.as<int32_t>(), cap, pairs_out, pcount, mol_count, ws.epoch)
+#define AICA_LAUNCH_R(MIX, COMP, ROT)                    \
+  do {                                                   \
+    if constexpr (MODE == 0) {                           \
+      if (split) AICA_LAUNCH_S(MIX, COMP, ROT, true);    \
+      else AICA_LAUNCH_S(MIX, COMP, ROT, false);         \
+    } else {                                             \
+      AICA_LAUNCH_S(MIX, COMP, ROT, false);              \
+    }                                                    \
+  } while (0)
 #define AICA_LAUNCH(MIX, COMP) AICA_LAUNCH_R(MIX, COMP, false)
   if (rot) {  // rotating referral: compensated sums always (the variants with a rotation are built once)
     if (nsp == 1) AICA_LAUNCH_R(0, true, true);
@@ -1620,6 +1637,7 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
   }
 #undef AICA_LAUNCH
 #undef AICA_LAUNCH_R
+#undef AICA_LAUNCH_S
   HIPCHK(hipGetLastError());
   return AICA_OK;
 }
