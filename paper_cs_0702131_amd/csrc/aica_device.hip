@@ -112,6 +112,9 @@ struct aica_dil {
   Neigh nb;
   DBuf d_nb_cell0, d_nb_run_off, d_nb_runs, d_nb_eB, d_nb_erev, d_nb_vec32, d_nb_vec64, d_nb_orig, d_nb_eoff;
   DBuf d_box;                   // [groups][6] box of each group's molecules in its frame (compute type)
+  // rotating referral: the groups of the full lists without a turned entry, then those with one
+  DBuf d_nb_glist;
+  int64_t nb_plain_groups = 0;
   DBuf d_rot64;                 // [27][9] rotation of every image code (only with rotational referral)
   // per step
   bool bin_valid = false;
@@ -1306,6 +1309,20 @@ static int ensure_groups(aica_dil *h, int64_t n) {
           v64[k] = make_double4(o[0], o[1], o[2], __builtin_bit_cast(double, (int64_t)code));
         }
     });
+    if (h->geo.has_rot) {
+      std::vector<int32_t> list, turned;
+      for (int64_t a = 0; a < N.ng; ++a) {
+        bool rot = false;
+        for (int64_t e = N.e_off[a]; e < N.e_off[a + 1] && !rot; ++e) {
+          const int c = N.e_code[e];
+          rot = image_transform(h->geo, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1).rot;
+        }
+        (rot ? turned : list).push_back((int32_t)a);
+      }
+      h->nb_plain_groups = (int64_t)list.size();
+      list.insert(list.end(), turned.begin(), turned.end());
+      if ((rc = upload(h->d_nb_glist, list))) return rc;
+    }
     if ((rc = upload(h->d_nb_cell0, N.cell0))) return rc;
     if ((rc = upload(h->d_nb_run_off, N.run_off))) return rc;
     if ((rc = upload(h->d_nb_runs, N.runs))) return rc;
@@ -1589,10 +1606,9 @@ template <typename T, int MODE>
 static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool comp, hipStream_t st, int64_t cap,
                        unsigned long long *pcount, int32_t *mol_count = nullptr) {
   using V4 = typename Vec4<T>::type;
-  const int64_t ng = h->grp.ng;
   constexpr int NW = pair_waves(sizeof(T));
-  // few groups: a whole block per group
-  const bool split = MODE == 0 && ng <= kSplitGroups;
+  const int64_t ng = h->grp.ng;
+  const bool split = MODE == 0 && ng <= kSplitGroups;  // few groups: a whole block per group
   const int64_t nblocks = split ? ng : (ng + NW - 1) / NW;
   const int64_t padded = ((nblocks + 7) / 8) * 8;
   const V4 *pos = (const V4 *)ws.pos;
@@ -1642,8 +1658,12 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
   return AICA_OK;
 }
 
+// The full lists, over all groups or (rotating referral) over the groups without (part 0) or with a turned entry (1):
+// the kernels with rotations hold fewer blocks per CU and form the pair vector in more steps, and only the groups along
+// the coupled sides need them (371,896-molecule wedge, FP32 adjoint: 284 us for all groups with rotations, 151 + 89 in
+// two launches).
 template <typename T>
-static NbLists nb_lists(const aica_dil *h) {
+static NbLists nb_lists(const aica_dil *h, int part) {
   NbLists nl;
   nl.cell0 = h->d_nb_cell0.as<int32_t>();
   nl.run_off = h->d_nb_run_off.as<int64_t>();
@@ -1654,7 +1674,12 @@ static NbLists nb_lists(const aica_dil *h) {
   nl.e_vec = sizeof(T) == 4 ? h->d_nb_vec32.p : h->d_nb_vec64.p;
   nl.e_vec64 = h->d_nb_vec64.as<double4>();
   nl.rot = h->geo.has_rot ? h->d_rot64.as<double>() : nullptr;
+  nl.list = nullptr;
   nl.ng = h->nb.ng;
+  if (h->geo.has_rot) {
+    nl.list = h->d_nb_glist.as<int32_t>() + (part ? h->nb_plain_groups : 0);
+    nl.ng = part ? h->nb.ng - h->nb_plain_groups : h->nb_plain_groups;
+  }
   return nl;
 }
 
@@ -1662,30 +1687,31 @@ static NbLists nb_lists(const aica_dil *h) {
 template <typename T>
 static int launch_force(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool comp, void *out, hipStream_t st) {
   using V4 = typename Vec4<T>::type;
-  const int64_t ng = h->nb.ng, padded = ((ng + 7) / 8) * 8;
-  const bool rot = h->geo.has_rot;
-  const NbLists nl = nb_lists<T>(h);
+  const int nsp = tab.nsp;
+  constexpr bool C = sizeof(T) == 4;  // compensated sums exist in FP32 only
 #define AICA_FORCE(MIX, COMP, ROT)                                                                                  \
   hipLaunchKernelGGL((k_force<T, MIX, COMP, ROT>), dim3((unsigned)padded), dim3(kNbThreads), 0, st, nl,             \
                      (const V4 *)ws.pos, (const T *)ws.box, h->d_cell_start.as<int32_t>(), h->d_perm.as<int32_t>(),  \
-                     padded, tab, (T *)out,                                                                           \
-                     (double *)ws.gpart, (unsigned long long *)ws.gnp)
-  const int nsp = tab.nsp;
-  constexpr bool C = sizeof(T) == 4;  // compensated sums exist in FP32 only
-  if (rot) {  // rotating referral: FP64 only (full_lists)
-    if constexpr (sizeof(T) == 8) {
-      if (nsp == 1) AICA_FORCE(0, false, true);
-      else if (nsp == 2) AICA_FORCE(1, false, true);
-      else AICA_FORCE(2, false, true);
+                     padded, tab, (T *)out, (double *)ws.gpart, (unsigned long long *)ws.gnp)
+  for (int part = 0; part < (h->geo.has_rot ? 2 : 1); ++part) {
+    const NbLists nl = nb_lists<T>(h, part);
+    const int64_t padded = ((nl.ng + 7) / 8) * 8;
+    if (nl.ng == 0) continue;
+    if (part == 1) {  // rotating referral: FP64 only (full_lists)
+      if constexpr (sizeof(T) == 8) {
+        if (nsp == 1) AICA_FORCE(0, false, true);
+        else if (nsp == 2) AICA_FORCE(1, false, true);
+        else AICA_FORCE(2, false, true);
+      }
+    } else if (C && comp) {
+      if (nsp == 1) AICA_FORCE(0, C, false);
+      else if (nsp == 2) AICA_FORCE(1, C, false);
+      else AICA_FORCE(2, C, false);
+    } else {
+      if (nsp == 1) AICA_FORCE(0, false, false);
+      else if (nsp == 2) AICA_FORCE(1, false, false);
+      else AICA_FORCE(2, false, false);
     }
-  } else if (C && comp) {
-    if (nsp == 1) AICA_FORCE(0, C, false);
-    else if (nsp == 2) AICA_FORCE(1, C, false);
-    else AICA_FORCE(2, C, false);
-  } else {
-    if (nsp == 1) AICA_FORCE(0, false, false);
-    else if (nsp == 2) AICA_FORCE(1, false, false);
-    else AICA_FORCE(2, false, false);
   }
 #undef AICA_FORCE
   HIPCHK(hipGetLastError());
@@ -1696,20 +1722,23 @@ static int launch_force(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool c
 template <typename T>
 static int launch_adj(aica_dil *h, const LJTab &tab, const AdjTab &at, void *out, hipStream_t st) {
   using V4 = typename Vec4<T>::type;
-  const int64_t ng = h->nb.ng, padded = ((ng + 7) / 8) * 8;
-  const NbLists nl = nb_lists<T>(h);
 #define AICA_LAUNCH_ADJ(MIX, ROT)                                                                                    \
   hipLaunchKernelGGL((k_force_adj<T, MIX, ROT>), dim3((unsigned)padded), dim3(kNbThreads), 0, st, nl,                \
                      h->d_pos.as<V4>(), h->d_gG.as<V4>(), h->d_box.as<T>(), h->d_cell_start.as<int32_t>(),           \
                      h->d_perm.as<int32_t>(), padded, tab, at, (T *)out, h->d_gpar.as<double>())
-  if (h->geo.has_rot) {
-    if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, true);
-    else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, true);
-    else AICA_LAUNCH_ADJ(2, true);
-  } else {
-    if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, false);
-    else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, false);
-    else AICA_LAUNCH_ADJ(2, false);
+  for (int part = 0; part < (h->geo.has_rot ? 2 : 1); ++part) {
+    const NbLists nl = nb_lists<T>(h, part);
+    const int64_t padded = ((nl.ng + 7) / 8) * 8;
+    if (nl.ng == 0) continue;
+    if (part == 1) {
+      if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, true);
+      else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, true);
+      else AICA_LAUNCH_ADJ(2, true);
+    } else {
+      if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, false);
+      else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, false);
+      else AICA_LAUNCH_ADJ(2, false);
+    }
   }
 #undef AICA_LAUNCH_ADJ
   HIPCHK(hipGetLastError());
