@@ -120,10 +120,11 @@ struct aica_dil {
   bool bin_valid = false;
   int64_t wsteps_groups = 0;  // groups whose wave-step counts d_gnp holds (a forward call on the current binning)
   int64_t n = 0;
+  unsigned long long *host_status = nullptr;    // pinned: the counts of a binning
   const void *bin_pos = nullptr;
   int32_t bin_dtype = 0;
   int64_t jtotal = 0;
-  DBuf d_cell_of, d_count, d_cell_start, d_rank, d_perm, d_g_start, d_mol_group, d_jcnt, d_slot_base, d_cell_sorted;
+  DBuf d_cell_of, d_count, d_cell_start, d_rank, d_perm, d_slot_base, d_cell_sorted;
   DBuf d_scan_tmp, d_status, d_slow;
   DBuf d_ref;                   // [n] float4 per caller molecule id: centre and radius of a ball that lies
                                 // inside the molecule's cell of the last binning (radius 0: none)
@@ -138,6 +139,9 @@ struct aica_dil {
   uint32_t epoch = 0;          // tag of the reaction records written by the current call
   size_t jpart_tagged = 0;     // bytes of d_jpart known to hold no valid tag
   std::map<std::string, Timer> timers;
+  ~aica_dil() {
+    if (host_status) (void)hipHostFree(host_status);
+  }
 };
 
 // =====================================================================================================
@@ -158,54 +162,45 @@ __device__ __forceinline__ double orient3(const double *a, const double *b, cons
 // from the cell (counts stored as doubles, exact).
 //
 // Is p inside the cell: some tetrahedron (cc, fc, v_k, v_k+1) contains p, with a relative tolerance tau
-// of that tetrahedron's volume (tau = 1e-12 for membership; the previous-cell fast path asks for
-// tau = -1e-9, i.e. strictly inside).  The four barycentric tests of tetrahedron k are: the outer face,
+// of that tetrahedron's volume (tau = 1e-12 for membership; the tests of the previous cell and its neighbours ask
+// for tau = -1e-9, i.e. strictly inside).  The four barycentric tests of tetrahedron k are: the outer face,
 // orient(p, fc, v_k, v_k+1) >= -tol; the edge plane through cc, orient(cc, p, v_k, v_k+1) >= -tol; and
-// the two spoke planes (cc, fc, v_k), (cc, fc, v_k+1), whose orientations s_k = orient(cc, fc, v_k, p)
-// are shared by neighbouring tetrahedra of the fan.  The face whose centroid direction from cc best
-// matches p - cc is tried first (the answer does not depend on the order).
-__device__ bool point_in_face_fan(const double *p, const double *cc, const double *fc, const double *V, int len,
-                                  double tau) {
-  double s_first = orient3(cc, fc, V, p), s_prev = s_first;
-  const double *vp = V;
-  for (int j = 0; j < len; ++j) {
-    const double *vn = V + 3 * (j + 1 == len ? 0 : j + 1);
-    const double s_next = (j + 1 == len) ? s_first : orient3(cc, fc, vn, p);
-    const double v = orient3(cc, fc, vp, vn);
-    const double tol = -tau * fabs(v);
-    if (s_prev >= tol && -s_next >= tol && orient3(p, fc, vp, vn) >= tol && orient3(cc, p, vp, vn) >= tol)
-      return true;
-    s_prev = s_next;
-    vp = vn;
-  }
-  return false;
-}
-
-__device__ bool point_in_rec(const double *p, const double *R, double tau) {
+// the two spoke planes (cc, fc, v_k), (cc, fc, v_k+1).  A group of 32 lanes deals the tetrahedra out (the same value
+// in the group's lanes).
+__device__ __forceinline__ bool point_in_rec(const double *p, const double *R, double tau) {
+  const int lane = (int)(threadIdx.x & 31), g0 = (int)(threadIdx.x & 32);
   const int nf = (int)R[0];
-  const double *cc = R + 1, *FC = R + 4, *LEN = FC + 3 * nf, *V = LEN + nf;
-  const double d0 = p[0] - cc[0], d1 = p[1] - cc[1], d2 = p[2] - cc[2];
-  int best = 0;
-  double bs = -1e300;
-  int64_t boff = 0, off = 0;
-  for (int k = 0; k < nf; ++k) {
-    const double e0 = FC[3 * k] - cc[0], e1 = FC[3 * k + 1] - cc[1], e2 = FC[3 * k + 2] - cc[2];
-    const double sc = (d0 * e0 + d1 * e1 + d2 * e2) / (e0 * e0 + e1 * e1 + e2 * e2);
-    if (sc > bs) {
-      bs = sc;
-      best = k;
-      boff = off;
+  const double cc[3] = {R[1], R[2], R[3]};
+  const double *FC = R + 4, *LEN = FC + 3 * nf, *V = LEN + nf;
+  bool in = false;
+  int off = 0;  // tetrahedra of the faces before kb
+  for (int kb = 0; kb < nf; kb += 32) {
+    const int m = min(nf - kb, 32);
+    const int len = lane < m ? (int)LEN[kb + lane] : 0;  // lane k: face kb + k
+    for (int t0 = 0, end = 1; t0 < end; t0 += 32) {
+      const int t = t0 + lane;  // the lane's tetrahedron, of face f, whose fl tetrahedra start at v0
+      int f = 0, v0 = 0, fl = 0;
+      end = 0;
+      for (int k = 0; k < m; ++k) {
+        const int lk = __shfl(len, g0 + k, 64);
+        if (t >= end) {
+          f = k;
+          v0 = end;
+          fl = lk;
+        }
+        end += lk;
+      }
+      if (t < end) {
+        const double *fc = FC + 3 * (int64_t)(kb + f), *vp = V + 3 * (int64_t)(off + t);
+        const double *vn = V + 3 * (int64_t)(off + (t + 1 == v0 + fl ? v0 : t + 1));
+        const double tol = -tau * fabs(orient3(cc, fc, vp, vn));
+        in = in || (orient3(cc, fc, vp, p) >= tol && -orient3(cc, fc, vn, p) >= tol && orient3(p, fc, vp, vn) >= tol &&
+                    orient3(cc, p, vp, vn) >= tol);
+      }
+      if (t0 + 32 >= end) off += end;
     }
-    off += 3 * (int64_t)LEN[k];
   }
-  if (point_in_face_fan(p, cc, FC + 3 * best, V + boff, (int)LEN[best], tau)) return true;
-  off = 0;
-  for (int k = 0; k < nf; ++k) {
-    const int len = (int)LEN[k];
-    if (k != best && point_in_face_fan(p, cc, FC + 3 * k, V + off, len, tau)) return true;
-    off += 3 * (int64_t)len;
-  }
-  return false;
+  return ((__builtin_amdgcn_ballot_w64(in) >> (threadIdx.x & 32)) & 0xFFFFFFFFull) != 0;
 }
 
 // FP32 copies of the cell records for the previous-cell test, fixed stride kR32 float4 per sorted cell:
@@ -226,95 +221,6 @@ __device__ __forceinline__ float orient3f(const float *a, const float *b, const 
   return u0 * (v1 * w2 - v2 * w1) + u1 * (v2 * w0 - v0 * w2) + u2 * (v0 * w1 - v1 * w0);
 }
 
-// across (optional): the sorted id of the cell across the face whose centroid direction best matches
-// p - cc (the face a molecule that left the cell has most likely crossed), -1 on a boundary face.
-__device__ bool surely_in_rec32(const double *p, const float4 *R, int *across = nullptr) {
-  const float4 h = R[0], h2 = R[1];
-  const int nf = (int)h.x;
-  const float pr[3] = {(float)(p[0] - (double)h.y), (float)(p[1] - (double)h.z), (float)(p[2] - (double)h.w)};
-  const float cc[3] = {h2.x, h2.y, h2.z};
-  // best face first (the answer does not depend on the order)
-  int best = 0, boff = 0, off = 0;
-  float bs = -3.0e38f;
-  for (int k = 0; k < nf; ++k) {
-    const float4 f = R[2 + k];
-    const float e0 = f.x - cc[0], e1 = f.y - cc[1], e2 = f.z - cc[2];
-    const float sc = ((pr[0] - cc[0]) * e0 + (pr[1] - cc[1]) * e1 + (pr[2] - cc[2]) * e2) / (e0 * e0 + e1 * e1 + e2 * e2);
-    if (sc > bs) {
-      bs = sc;
-      best = k;
-      boff = off;
-    }
-    off += (int)f.w;
-  }
-  if (across) *across = __float_as_int(R[2 + nf + boff].w);
-  auto fan = [&](int k, int voff) -> bool {
-    const float4 f = R[2 + k];
-    const float fc[3] = {f.x, f.y, f.z};
-    const int len = (int)f.w;
-    const float4 *V = R + 2 + nf + voff;
-    float vp[3] = {V[0].x, V[0].y, V[0].z};
-    const float s_first = orient3f(cc, fc, vp, pr);
-    float s_prev = s_first;
-    for (int j = 0; j < len; ++j) {
-      const float4 n4 = V[j + 1 == len ? 0 : j + 1];
-      const float vn[3] = {n4.x, n4.y, n4.z};
-      const float s_next = (j + 1 == len) ? s_first : orient3f(cc, fc, vn, pr);
-      const float tol = 1e-4f * fabsf(orient3f(cc, fc, vp, vn));
-      if (s_prev > tol && -s_next > tol && orient3f(pr, fc, vp, vn) > tol && orient3f(cc, pr, vp, vn) > tol)
-        return true;
-      s_prev = s_next;
-      vp[0] = vn[0];
-      vp[1] = vn[1];
-      vp[2] = vn[2];
-    }
-    return false;
-  };
-  if (fan(best, boff)) return true;
-  off = 0;
-  for (int k = 0; k < nf; ++k) {
-    const int len = (int)R[2 + k].w;
-    if (k != best && fan(k, off)) return true;
-    off += len;
-  }
-  return false;
-}
-
-// Radius of a ball about p that lies inside the cell of FP32 record R, for a p that the record shows
-// strictly inside: the cell's boundary is made of the face-fan triangles, and the distance from p to a
-// triangle is at least the distance to its plane, so the smallest plane distance bounds the distance to
-// the boundary from below.  FP32 rounding is covered by a margin of 1e-4 of the cell's size.  Returns the
-// ball as (centre rounded to FP32, radius reduced by that rounding); radius 0 when nothing is left.
-__device__ float4 inner_ball(const double *p, const float4 *R) {
-  const float4 h = R[0], h2 = R[1];
-  const int nf = (int)h.x;
-  const float pr[3] = {(float)(p[0] - (double)h.y), (float)(p[1] - (double)h.z), (float)(p[2] - (double)h.w)};
-  float dmin = 3.0e38f, size = 0.f;
-  int off = 0;
-  for (int k = 0; k < nf; ++k) {
-    const float4 f = R[2 + k];
-    const int len = (int)f.w;
-    const float e0 = f.x - h2.x, e1 = f.y - h2.y, e2 = f.z - h2.z;
-    size = fmaxf(size, sqrtf(e0 * e0 + e1 * e1 + e2 * e2));
-    const float4 *V = R + 2 + nf + off;
-    for (int j = 0; j < len; ++j) {
-      const float4 va = V[j], vb = V[j + 1 == len ? 0 : j + 1];
-      const float a0 = va.x - f.x, a1 = va.y - f.y, a2 = va.z - f.z;
-      const float b0 = vb.x - f.x, b1 = vb.y - f.y, b2 = vb.z - f.z;
-      const float n0 = a1 * b2 - a2 * b1, n1 = a2 * b0 - a0 * b2, n2 = a0 * b1 - a1 * b0;
-      const float nn = sqrtf(n0 * n0 + n1 * n1 + n2 * n2);
-      const float dd = fabsf(n0 * (pr[0] - f.x) + n1 * (pr[1] - f.y) + n2 * (pr[2] - f.z));
-      if (nn > 0.f) dmin = fminf(dmin, dd / nn);
-      else dmin = 0.f;
-    }
-    off += len;
-  }
-  const float pc[3] = {(float)p[0], (float)p[1], (float)p[2]};
-  const double s0 = p[0] - (double)pc[0], s1 = p[1] - (double)pc[1], s2 = p[2] - (double)pc[2];
-  const double r = (double)dmin * (1.0 - 1e-6) - 1e-4 * (double)size - sqrt(s0 * s0 + s1 * s1 + s2 * s2);
-  return make_float4(pc[0], pc[1], pc[2], r > 0 ? (float)r : 0.f);
-}
-
 // Plane records: per sorted cell kPl float4 (n, d), one per boundary triangle of the cell's face fans: the
 // inward unit normal n and d = n.(f - a) for a point f of the triangle, in the frame a of the cell's FP32
 // record, so that n.(p - a) - d is the signed distance of p from the triangle's plane (positive inside).
@@ -322,6 +228,92 @@ __device__ float4 inner_ball(const double *p, const float4 *R) {
 // so that its test never accepts.
 constexpr int kPl = 24;
 
+// The FP32 tests of one molecule by a group of 32 lanes, a boundary triangle (and its tetrahedron) per lane: the lanes
+// read a record in a few wide loads and no lane walks the faces in turn.  With the fixed stride of the records a cell
+// has at most 7 faces and 24 triangles.
+struct RecLane {
+  float f[3], vp[3], vn[3];  // this lane's triangle: face centroid and two consecutive vertices, relative to a
+  float pr[3], cc[3];
+  bool on;                   // the lane has a triangle
+  int32_t across;            // the cell across the face whose centroid direction best matches p - cc (-1: boundary)
+};
+__device__ __forceinline__ RecLane load_rec32(const double *p, const float4 *R) {
+  const int c = (int)(threadIdx.x & 31), g0 = (int)(threadIdx.x & 32);
+  const float4 h = R[0], h2 = R[1];
+  const int nf = (int)h.x;
+  RecLane r;
+  r.pr[0] = (float)(p[0] - (double)h.y);
+  r.pr[1] = (float)(p[1] - (double)h.z);
+  r.pr[2] = (float)(p[2] - (double)h.w);
+  r.cc[0] = h2.x;
+  r.cc[1] = h2.y;
+  r.cc[2] = h2.z;
+  const float4 fk = c < nf ? R[2 + c] : make_float4(0.f, 0.f, 0.f, 0.f);  // lane k: face k
+  // the lane's triangle: face `face` starts at vertex v0 of the list and has len of them
+  int face = 0, v0 = 0, len = 0, off = 0;
+  float bs = -3.0e38f;
+  int boff = 0;
+  const float e0 = fk.x - r.cc[0], e1 = fk.y - r.cc[1], e2 = fk.z - r.cc[2];
+  const float sc = c < nf ? ((r.pr[0] - r.cc[0]) * e0 + (r.pr[1] - r.cc[1]) * e1 + (r.pr[2] - r.cc[2]) * e2) /
+                                (e0 * e0 + e1 * e1 + e2 * e2)
+                          : -3.0e38f;
+  for (int k = 0; k < nf; ++k) {
+    const int lk = (int)__shfl(fk.w, g0 + k, 64);
+    const float sk = __shfl(sc, g0 + k, 64);
+    if (c >= off) {
+      face = k;
+      v0 = off;
+      len = lk;
+    }
+    if (sk > bs) {
+      bs = sk;
+      boff = off;
+    }
+    off += lk;
+  }
+  r.on = c < off;
+  r.f[0] = __shfl(fk.x, g0 + face, 64);
+  r.f[1] = __shfl(fk.y, g0 + face, 64);
+  r.f[2] = __shfl(fk.z, g0 + face, 64);
+  const float4 *V = R + 2 + nf;
+  const int j = r.on ? c : 0, jn = r.on ? (c + 1 == v0 + len ? v0 : c + 1) : 0;
+  const float4 a = V[j], b = V[jn];
+  r.vp[0] = a.x;
+  r.vp[1] = a.y;
+  r.vp[2] = a.z;
+  r.vn[0] = b.x;
+  r.vn[1] = b.y;
+  r.vn[2] = b.z;
+  r.across = __float_as_int(__shfl(a.w, g0 + boff, 64));
+  return r;
+}
+// Some tetrahedron surely contains the point (the margin at kR32); the same value in all 32 lanes.
+__device__ __forceinline__ bool rec_lanes_inside(const RecLane &r) {
+  const float tol = 1e-4f * fabsf(orient3f(r.cc, r.f, r.vp, r.vn));
+  const bool in = r.on && orient3f(r.cc, r.f, r.vp, r.pr) > tol && -orient3f(r.cc, r.f, r.vn, r.pr) > tol &&
+                  orient3f(r.pr, r.f, r.vp, r.vn) > tol && orient3f(r.cc, r.pr, r.vp, r.vn) > tol;
+  return ((__builtin_amdgcn_ballot_w64(in) >> (threadIdx.x & 32)) & 0xFFFFFFFFull) != 0;
+}
+// Radius of a ball about p that lies inside the cell of FP32 record R, for a p that the record shows
+// strictly inside (a triangle per lane): the cell's boundary is made of the face-fan triangles, and the distance from p to a
+// triangle is at least the distance to its plane, so the smallest plane distance bounds the distance to
+// the boundary from below.  FP32 rounding is covered by a margin of 1e-4 of the cell's size.  Returns the
+// ball as (centre rounded to FP32, radius reduced by that rounding); radius 0 when nothing is left.
+__device__ __forceinline__ float4 rec_lanes_ball(const RecLane &r, const double *p, const float4 *R) {
+  const float a0 = r.vp[0] - r.f[0], a1 = r.vp[1] - r.f[1], a2 = r.vp[2] - r.f[2];
+  const float b0 = r.vn[0] - r.f[0], b1 = r.vn[1] - r.f[1], b2 = r.vn[2] - r.f[2];
+  const float n0 = a1 * b2 - a2 * b1, n1 = a2 * b0 - a0 * b2, n2 = a0 * b1 - a1 * b0;
+  const float nn = sqrtf(n0 * n0 + n1 * n1 + n2 * n2);
+  const float dd = fabsf(n0 * (r.pr[0] - r.f[0]) + n1 * (r.pr[1] - r.f[1]) + n2 * (r.pr[2] - r.f[2]));
+  float dmin = r.on ? (nn > 0.f ? dd / nn : 0.f) : 3.0e38f;
+#pragma unroll
+  for (int o = 1; o < 32; o <<= 1) dmin = fminf(dmin, __shfl_xor(dmin, o, 64));
+  const float size = R[1].w;  // the largest distance from the vertex mean to a face centroid
+  const float pc[3] = {(float)p[0], (float)p[1], (float)p[2]};
+  const double s0 = p[0] - (double)pc[0], s1 = p[1] - (double)pc[1], s2 = p[2] - (double)pc[2];
+  const double rad = (double)dmin * (1.0 - 1e-6) - 1e-4 * (double)size - sqrt(s0 * s0 + s1 * s1 + s2 * s2);
+  return make_float4(pc[0], pc[1], pc[2], rad > 0 ? (float)rad : 0.f);
+}
 // A point on the inner side of every boundary triangle's plane is strictly inside the cell: from a point
 // outside the cell (or on its boundary), a segment to an interior point enters the cell through some
 // boundary triangle, so that point lies on the outer side of (or on) the triangle's plane.  Accepts p when
@@ -330,16 +322,22 @@ constexpr int kPl = 24;
 // inside: radius = that distance less the margin and the centre's rounding.  A point inside but not this
 // far from every plane (near the boundary, or beside a reflex crease of a non-convex cell) is left to the
 // fan test.
-__device__ bool plane_ball(const double *p, const float4 *R, const float4 *PL, float4 &ball) {
+// A group of LANES lanes (a power of two) deals the planes out.
+template <int LANES>
+__device__ __forceinline__ bool plane_ball(const double *p, const float4 *R, const float4 *PL, float4 &ball) {
+  const int c = (int)(threadIdx.x & (LANES - 1));
   const float4 h = R[0];
   const float size = R[1].w;
   const float pr0 = (float)(p[0] - (double)h.y), pr1 = (float)(p[1] - (double)h.z), pr2 = (float)(p[2] - (double)h.w);
   float smin = 3.0e38f;
-#pragma unroll 8
-  for (int k = 0; k < kPl; ++k) {
-    const float4 q = PL[k];
+#pragma unroll
+  for (int k = 0; k < (kPl + LANES - 1) / LANES; ++k) {
+    const int i = k * LANES + c;
+    const float4 q = PL[i < kPl ? i : 0];
     smin = fminf(smin, fmaf(q.x, pr0, fmaf(q.y, pr1, fmaf(q.z, pr2, -q.w))));
   }
+#pragma unroll
+  for (int o = 1; o < LANES; o <<= 1) smin = fminf(smin, __shfl_xor(smin, o, 64));
   if (!(smin > 1e-4f * size)) return false;
   const float pc[3] = {(float)p[0], (float)p[1], (float)p[2]};
   const double s0 = p[0] - (double)pc[0], s1 = p[1] - (double)pc[1], s2 = p[2] - (double)pc[2];
@@ -350,13 +348,15 @@ __device__ bool plane_ball(const double *p, const float4 *R, const float4 *PL, f
 
 // Locate each molecule: cell_of[i] = sorted index of the cell that contains x_i, in two kernels so that
 // the rare slow cases do not hold up whole waves.
-// k_locate_fast visits molecules in the order trav (the previous binning's sorted order, so that
-// neighbouring threads read neighbouring cell records), kLocPerLane per lane: a molecule still inside the
-// ball kept from its last record test is in its previous cell (hint); the others are compacted in LDS and
-// tested 64 at a time against the FP32 records (the previous cell, then the cell across the face most
-// likely crossed: a molecule that a record shows strictly inside a cell is in no other); every other
-// molecule goes to a list.  k_locate_slow takes that list, a group of lanes per molecule: the FP64 previous-cell
-// test and the cells across the previous cell's faces (a molecule that left its cell has crossed one of
+// k_locate_fast visits molecules in the order trav (the previous binning's sorted order, so that neighbouring threads
+// read neighbouring cell records), MPB per block, in three phases over lists in LDS: a molecule still inside the ball
+// kept from its last record test is in its previous cell (hint), one lane each; the others take the plane test of that
+// cell, eight lanes each; what it does not accept takes the FP32 fan of that cell, then both tests of the cell across
+// the face most likely crossed, 32 lanes each (a molecule that a record shows strictly inside a cell is in no other);
+// every other molecule goes to a list.  What bounds the record tests is the latency of their loads: with one lane per
+// molecule (24 planes and up to 24 tetrahedra in turn) this kernel took 39 us on 864 molecules and 0.68 ms on 6.7
+// million, in this form 10 us and 0.54 ms.  k_locate_slow takes the list, a group of lanes per molecule: the FP64
+// previous-cell test and the cells across the previous cell's faces (a molecule that left its cell has crossed one of
 // them: the paper's membership tracking), each accepted only when the point is strictly inside; then
 // every cell whose padded box holds the point, in ascending mesh cell id (the lowest containing cell wins
 // a tie on a shared face, edge or vertex).  Without FP32 records (a cell too large for the fixed stride)
@@ -365,188 +365,165 @@ __device__ bool plane_ball(const double *p, const float4 *R, const float4 *PL, f
 // (trav[t] = its caller index, hint[t] = its previous cell; without a previous binning t is the
 // caller index and there is no hint), so that only the positions are read out of order.
 constexpr int kRouteSlots = 64;
+// Molecules per block.  256 fill the block's lanes in every phase; up to two such blocks per CU (131,072 molecules) 32
+// give each CU more of the record tests' loads in flight.  A binning (device time) with 32 / 256: 13,440 molecules 51 /
+// 58 us, 100,000 77 / 80, 60,001 in cells of a hundred 97 / 88, 219,488 92 / 86, 371,896 117 / 99.
+constexpr int kMpb = 256, kMpbFew = 32;
+constexpr int64_t kFewMolecules = 131072;
 
-constexpr int kLocPerLane = 4;  // molecules per lane in the fast kernel
-
-template <typename PT>
+template <typename PT, int MPB>
 __global__ __launch_bounds__(256) void k_locate_fast(
     const PT *__restrict__ pos, int64_t n, const int32_t *__restrict__ trav, const int32_t *__restrict__ hint,
     const float4 *__restrict__ rec32, const float4 *__restrict__ pl32, float4 *__restrict__ ref,
     int32_t *__restrict__ cell_t, int32_t *__restrict__ rank_t, int32_t *__restrict__ count,
     unsigned long long *__restrict__ nslow, int32_t *__restrict__ slow, unsigned long long *__restrict__ routes) {
-  constexpr int kSpan = 64 * kLocPerLane;  // molecules per wave
-  __shared__ int32_t rec_l[4][kSpan];      // per wave: slots (relative to the wave's first) for the records
-  __shared__ int32_t slow_l[4][kSpan];     // per wave: slots for the slow kernel
-  const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
-  const int64_t base = ((int64_t)blockIdx.x * 4 + w) * kSpan;
-  int nr = 0, ns = 0;  // wave-uniform list lengths
-  auto push = [&](int32_t *L, int &len, bool take, int val) {
-    const unsigned long long m = __builtin_amdgcn_ballot_w64(take);
-    if (take) L[len + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = val;
-    len += (int)__builtin_popcountll(m);
+  // molecules (relative to the block's first) for the plane test, for the fan, and for the slow kernel
+  __shared__ int32_t plane_l[MPB], fan_l[MPB], slow_l[MPB];
+  __shared__ int32_t np, nf, ns, nrec;
+  __shared__ unsigned long long start;
+  const int tid = (int)threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.x * MPB;
+  if (tid == 0) np = nf = ns = nrec = 0;
+  __syncthreads();
+  auto take = [&](int64_t t, int64_t i, int32_t c, const float4 *ball) {
+    if (ball) ref[i] = *ball;
+    cell_t[t] = c;
+    rank_t[t] = atomicAdd(&count[c], 1);
   };
-  // ---- the ball test, kLocPerLane molecules per lane
-  for (int k = 0; k < kLocPerLane; ++k) {
-    const int off = k * 64 + lane;
+  // ---- the ball test
+#pragma unroll
+  for (int k = 0; k < (MPB + 255) / 256; ++k) {
+    const int off = k * 256 + tid;
     const int64_t t = base + off;
-    int how = -1;  // 0: inside its ball, 1: to the record test, 2: to the slow kernel
-    if (t < n) {
+    if ((MPB >= 256 || off < MPB) && t < n) {
       const int64_t i = trav ? trav[t] : t;
       const double p[3] = {(double)pos[3 * i], (double)pos[3 * i + 1], (double)pos[3 * i + 2]};
       const int32_t h0 = hint ? hint[t] : -1;
-      how = 2;
+      bool rec = false, ball = false;
       if (h0 >= 0 && isfinite(p[0]) && isfinite(p[1]) && isfinite(p[2])) {
         // still inside the ball found inside this cell when it was last tested: no record needed
         const float4 b = ref[i];
         const double e0 = p[0] - (double)b.x, e1 = p[1] - (double)b.y, e2 = p[2] - (double)b.z;
-        if (b.w > 0.f && e0 * e0 + e1 * e1 + e2 * e2 < (double)b.w * (double)b.w) {
-          how = 0;
-          cell_t[t] = h0;
-          rank_t[t] = atomicAdd(&count[h0], 1);
-        } else if (rec32) {
-          how = 1;
-        }
+        ball = b.w > 0.f && e0 * e0 + e1 * e1 + e2 * e2 < (double)b.w * (double)b.w;
+        rec = !ball && rec32;
       }
+      if (ball) take(t, i, h0, nullptr);
+      else if (rec) plane_l[atomicAdd(&np, 1)] = off;
+      else slow_l[atomicAdd(&ns, 1)] = off;
     }
-    push(rec_l[w], nr, how == 1, off);
-    push(slow_l[w], ns, how == 2, off);
   }
-  wave_lds_sync();
-  // ---- the FP32 records of the molecules that left their ball, 64 at a time on a compacted list: the
-  // previous cell, then the cell across the face most likely crossed
-  int nrec = 0;
-  for (int b = 0; b < nr; b += 64) {
-    int how = -1;
-    int off = 0;
-    if (b + lane < nr) {
-      off = rec_l[w][b + lane];
-      const int64_t t = base + off;
-      const int64_t i = trav[t];
-      const double p[3] = {(double)pos[3 * i], (double)pos[3 * i + 1], (double)pos[3 * i + 2]};
-      const int32_t h0 = hint[t];
-      int32_t found = -1, across = -1;
-      float4 ball;
-      bool have_ball = false;  // the plane test accepted and gave the ball
-      if (pl32 && plane_ball(p, rec32 + (int64_t)kR32 * h0, pl32 + (int64_t)kPl * h0, ball)) {
-        found = h0;
-        have_ball = true;
-      } else if (surely_in_rec32(p, rec32 + (int64_t)kR32 * h0, &across)) {
-        found = h0;
-      } else if (across >= 0) {
-        if (pl32 && plane_ball(p, rec32 + (int64_t)kR32 * across, pl32 + (int64_t)kPl * across, ball)) {
-          found = across;
-          have_ball = true;
-        } else if (surely_in_rec32(p, rec32 + (int64_t)kR32 * across)) {
-          found = across;
-        }
-      }
-      if (found >= 0) {
-        how = 1;
-        ref[i] = have_ball ? ball : inner_ball(p, rec32 + (int64_t)kR32 * found);
-        cell_t[t] = found;
-        rank_t[t] = atomicAdd(&count[found], 1);
+  __syncthreads();
+  // ---- the plane test of the previous cell, eight lanes per molecule (the group's lanes stay together)
+  for (int k = tid >> 3; k < np; k += 32) {
+    const int off = plane_l[k];
+    const int64_t t = base + off;
+    const int64_t i = trav[t];
+    const double p[3] = {(double)pos[3 * i], (double)pos[3 * i + 1], (double)pos[3 * i + 2]};
+    const int32_t h0 = hint[t];
+    float4 ball;
+    const bool in = plane_ball<8>(p, rec32 + (int64_t)kR32 * h0, pl32 + (int64_t)kPl * h0, ball);
+    if ((tid & 7) == 0) {
+      if (in) {
+        take(t, i, h0, &ball);
+        atomicAdd(&nrec, 1);
       } else {
-        how = 2;
+        fan_l[atomicAdd(&nf, 1)] = off;
       }
     }
-    nrec += (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(how == 1));
-    push(slow_l[w], ns, how == 2, off);
   }
-  wave_lds_sync();
-  // ---- the wave's share of the slow list (one atomic), and of the route counters (spread over
-  // kRouteSlots addresses so that the waves do not queue on one)
+  __syncthreads();
+  // ---- the fan of the previous cell, then the cell across the face most likely crossed, 32 lanes per molecule
+  for (int k = tid >> 5; k < nf; k += 8) {
+    const int off = fan_l[k];
+    const int64_t t = base + off;
+    const int64_t i = trav[t];
+    const double p[3] = {(double)pos[3 * i], (double)pos[3 * i + 1], (double)pos[3 * i + 2]};
+    const int32_t h0 = hint[t];
+    const float4 *R = rec32 + (int64_t)kR32 * h0;
+    int32_t found = -1;
+    float4 ball;
+    const RecLane r = load_rec32(p, R);
+    if (rec_lanes_inside(r)) {
+      found = h0;
+      ball = rec_lanes_ball(r, p, R);
+    } else if (r.across >= 0) {
+      const float4 *Ra = rec32 + (int64_t)kR32 * r.across;
+      if (plane_ball<32>(p, Ra, pl32 + (int64_t)kPl * r.across, ball)) {
+        found = r.across;
+      } else {
+        const RecLane ra = load_rec32(p, Ra);
+        if (rec_lanes_inside(ra)) {
+          found = r.across;
+          ball = rec_lanes_ball(ra, p, Ra);
+        }
+      }
+    }
+    if ((tid & 31) == 0) {
+      if (found >= 0) {
+        take(t, i, found, &ball);
+        atomicAdd(&nrec, 1);
+      } else {
+        slow_l[atomicAdd(&ns, 1)] = off;
+      }
+    }
+  }
+  __syncthreads();
+  // ---- the block's share of the slow list (one atomic), and of the route counters (spread over kRouteSlots addresses
+  // so that the blocks do not queue on one)
   if (ns > 0) {
-    unsigned long long start = 0;
-    if (lane == 0) start = atomicAdd(nslow, (unsigned long long)ns);
-    start = __shfl(start, 0, 64);
-    for (int b = lane; b < ns; b += 64) slow[start + b] = (int32_t)(base + slow_l[w][b]);
+    if (tid == 0) start = atomicAdd(nslow, (unsigned long long)ns);
+    __syncthreads();
+    for (int b = tid; b < ns; b += 256) slow[start + b] = (int32_t)(base + slow_l[b]);
   }
-  if (lane == 0 && nrec > 0)
-    atomicAdd(routes + (blockIdx.x * 4 + w) % kRouteSlots, (unsigned long long)nrec);
+  if (tid == 0 && nrec > 0) atomicAdd(routes + blockIdx.x % kRouteSlots, (unsigned long long)nrec);
 }
 
-// The slow path for one molecule at p with previous cell h0 (-1: none): the previous cell and the cells
-// across its faces, each accepted only when p is strictly inside (so at most one accepts), then the cells of
-// the background bin whose padded box holds p, in ascending mesh cell id, the first containing one.  LANES
-// (16 or 64) > 1: a group of that many lanes (a whole wave, or four molecules per wave) tests that many
-// candidates side by side (the lowest accepting lane is the first accepting candidate, so the answer is that
-// of testing them one after another); every branch below depends only on values shared by the group, so its
-// lanes stay together.  With FP32 records the cells across the faces are first tried with the FP32 test,
-// which only accepts points strictly inside.  LANES = 1: one lane tests the candidates in turn.
-template <int LANES>
-__device__ int32_t slow_find(const double *p, int32_t h0, const float4 *__restrict__ rec32, const float4 *__restrict__ pl32,
-                             const int64_t *__restrict__ rec_off, const double *__restrict__ rec,
-                             const int64_t *__restrict__ nbr_off, const int32_t *__restrict__ nbr,
-                             const double *__restrict__ bb, const int64_t *__restrict__ gb_off,
-                             const int32_t *__restrict__ gb_cell, double glo0, double glo1, double glo2, double gh,
-                             int64_t nb0, int64_t nb1, int64_t nb2) {
-  constexpr bool WAVE = LANES > 1;
-  constexpr int kStep = LANES;
-  const int lane = WAVE ? (int)(threadIdx.x & (LANES - 1)) : 0;
-  const int g0lane = WAVE ? (int)(threadIdx.x & 63) - lane : 0;  // first lane of this molecule's group
-  int32_t found = -1;
-  // one round of candidate tests: k-th candidate c(k) for k < kc, test(c) -> accepted
-  auto round = [&](int64_t b, int64_t kc, auto cand, auto test) {
-    const int64_t k = b + lane;
-    int32_t c = -1;
-    bool in = false;
-    if (k < kc) {
-      c = cand(k);
-      in = test(c);
+// The slow path for one molecule at p with previous cell h0 (-1: none), by a group of 32 lanes.  The previous cell
+// and the cells across its faces, each accepted only when p is strictly inside (so at most one accepts), then the
+// cells of the background bin whose padded box holds p, in ascending mesh cell id, the first containing one.  The
+// lanes test 32 boxes at a time and then the tetrahedra of one cell, three loads deep: what bounds the kernel is the
+// chain of loads of its longest molecule.  Cells by lane, one tetrahedron after another, it took 45 to 65 us for the
+// few hundred molecules of a step of 13,440 to 100,000, and a first binning of 371,896 1.1 ms (now 0.65), of 6.7
+// million 15.8 ms (10.1).
+__device__ int32_t slow_find(const double *p, int32_t h0, const int64_t *__restrict__ rec_off,
+                             const double *__restrict__ rec, const int64_t *__restrict__ nbr_off,
+                             const int32_t *__restrict__ nbr, const double *__restrict__ bb,
+                             const int64_t *__restrict__ gb_off, const int32_t *__restrict__ gb_cell, double glo0,
+                             double glo1, double glo2, double gh, int64_t nb0, int64_t nb1, int64_t nb2) {
+  const int lane = (int)(threadIdx.x & 31), g0 = (int)(threadIdx.x & 32);
+  // the first of cand[b .. e) (in order) whose box holds p and whose tetrahedra do, with tolerance tau
+  auto first_of = [&](const int32_t *cand, int64_t b, int64_t e, double tau) -> int32_t {
+    for (int64_t k = b; k < e; k += 32) {
+      int32_t c = -1;
+      bool box = false;
+      if (k + lane < e) {
+        c = cand[k + lane];
+        const double *B = bb + 6 * (int64_t)c;
+        box = !(p[0] < B[0] || p[1] < B[1] || p[2] < B[2] || p[0] > B[3] || p[1] > B[4] || p[2] > B[5]);
+      }
+      unsigned hits = (unsigned)(__builtin_amdgcn_ballot_w64(box) >> g0);
+      while (hits) {
+        const int32_t d = __shfl(c, g0 + __builtin_ctz(hits), 64);
+        if (point_in_rec(p, rec + rec_off[d], tau)) return d;
+        hits &= hits - 1;
+      }
     }
-    if constexpr (WAVE) {
-      const unsigned long long m =
-          LANES == 64 ? __builtin_amdgcn_ballot_w64(in) : (__builtin_amdgcn_ballot_w64(in) >> g0lane) & ((1ull << LANES) - 1);
-      if (m) found = __shfl(c, g0lane + (int)__builtin_ctzll(m), 64);
-    } else if (in) {
-      found = c;
-    }
+    return -1;
   };
   if (h0 >= 0) {
-    const int64_t k0 = nbr_off[h0], kc = nbr_off[h0 + 1] - k0 + 1;  // the previous cell and its neighbours
-    auto cand = [&](int64_t k) { return k == 0 ? h0 : nbr[k0 + k - 1]; };
-    float4 ball;
-    if (WAVE && pl32)
-      for (int64_t b = 0; b < kc && found < 0; b += kStep)
-        round(b, kc, cand, [&](int32_t c) { return plane_ball(p, rec32 + (int64_t)kR32 * c, pl32 + (int64_t)kPl * c, ball); });
-    if (WAVE && rec32)
-      for (int64_t b = 0; b < kc && found < 0; b += kStep)
-        round(b, kc, cand, [&](int32_t c) { return surely_in_rec32(p, rec32 + (int64_t)kR32 * c); });
-    for (int64_t b = 0; b < kc && found < 0; b += kStep)
-      round(b, kc, cand, [&](int32_t c) { return point_in_rec(p, rec + rec_off[c], -1e-9); });
+    if (point_in_rec(p, rec + rec_off[h0], -1e-9)) return h0;
+    const int32_t c = first_of(nbr, nbr_off[h0], nbr_off[h0 + 1], -1e-9);
+    if (c >= 0) return c;
   }
-  if (found < 0) {
-    const double f0 = floor((p[0] - glo0) / gh), f1 = floor((p[1] - glo1) / gh), f2 = floor((p[2] - glo2) / gh);
-    if (f0 >= 0 && f1 >= 0 && f2 >= 0 && f0 < (double)nb0 && f1 < (double)nb1 && f2 < (double)nb2) {
-      const int64_t bin = (int64_t)f0 + nb0 * ((int64_t)f1 + nb1 * (int64_t)f2);
-      const int64_t g0 = gb_off[bin], g1 = gb_off[bin + 1];
-      // a cell whose planes show the point strictly inside is the only cell that holds it
-      if (pl32) {
-        float4 ball;
-        for (int64_t b = 0; b < g1 - g0 && found < 0; b += kStep)
-          round(b, g1 - g0, [&](int64_t k) { return gb_cell[g0 + k]; }, [&](int32_t c) {
-            const double *B = bb + 6 * (int64_t)c;
-            if (p[0] < B[0] || p[1] < B[1] || p[2] < B[2] || p[0] > B[3] || p[1] > B[4] || p[2] > B[5]) return false;
-            return plane_ball(p, rec32 + (int64_t)kR32 * c, pl32 + (int64_t)kPl * c, ball);
-          });
-      }
-      for (int64_t b = 0; b < g1 - g0 && found < 0; b += kStep)
-        round(b, g1 - g0, [&](int64_t k) { return gb_cell[g0 + k]; }, [&](int32_t c) {
-          const double *B = bb + 6 * (int64_t)c;
-          if (p[0] < B[0] || p[1] < B[1] || p[2] < B[2] || p[0] > B[3] || p[1] > B[4] || p[2] > B[5]) return false;
-          return point_in_rec(p, rec + rec_off[c], 1e-12);
-        });
-    }
-  }
-  return found;
+  const double f0 = floor((p[0] - glo0) / gh), f1 = floor((p[1] - glo1) / gh), f2 = floor((p[2] - glo2) / gh);
+  if (!(f0 >= 0 && f1 >= 0 && f2 >= 0 && f0 < (double)nb0 && f1 < (double)nb1 && f2 < (double)nb2)) return -1;
+  const int64_t bin = (int64_t)f0 + nb0 * ((int64_t)f1 + nb1 * (int64_t)f2);
+  return first_of(gb_cell, gb_off[bin], gb_off[bin + 1], 1e-12);
 }
 
-// The slow kernel.  Molecules that have a previous cell: LANES (16 or 64) lanes per molecule; otherwise (the
-// first binning, where every molecule comes here) LANES = 1, one thread per molecule.  A fixed grid strides
-// over the list, whose length is only known on the device.  A group of 16 lanes keeps four molecules in
-// flight per wave, which pays when the list is longer than the grid's waves; with fewer molecules a whole
-// wave per molecule ends sooner (a wave of four molecules runs their different paths one after another).
-template <typename PT, int LANES>
+// The slow kernel, two molecules per wave (at the first binning every molecule comes here).  A fixed grid strides over
+// the list, whose length is only known on the device; a short list is spread over the waves first.
+template <typename PT>
 __global__ __launch_bounds__(256) void k_locate_slow(
     const PT *__restrict__ pos, const unsigned long long *__restrict__ nslow, const int32_t *__restrict__ slow,
     const int32_t *__restrict__ trav, const int32_t *__restrict__ hint, const float4 *__restrict__ rec32,
@@ -557,26 +534,24 @@ __global__ __launch_bounds__(256) void k_locate_slow(
     int64_t nb2, float4 *__restrict__ ref, int32_t *__restrict__ cell_t, int32_t *__restrict__ rank_t,
     int32_t *__restrict__ count, unsigned long long *__restrict__ status) {
   const int64_t ns = (int64_t)*nslow;
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, gsize = (int64_t)gridDim.x * blockDim.x;
-  constexpr int kSh = __builtin_ctz(LANES);
-  const int64_t u0 = gid >> kSh, ustep = gsize >> kSh;
-  for (int64_t u = u0; u < ns; u += ustep) {  // uniform in each lane group
+  const int64_t nw = (int64_t)gridDim.x * 4, wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  for (int64_t u = wave + (threadIdx.x & 32 ? nw : 0); u < ns; u += 2 * nw) {  // uniform in each half wave
     const int64_t t = slow[u];
     const int64_t i = trav ? trav[t] : t;
     const double p[3] = {(double)pos[3 * i], (double)pos[3 * i + 1], (double)pos[3 * i + 2]};
     int32_t found = -1;
     if (isfinite(p[0]) && isfinite(p[1]) && isfinite(p[2]))
-      found = slow_find<LANES>(p, hint ? hint[t] : -1, rec32, pl32, rec_off, rec, nbr_off, nbr, bb, gb_off, gb_cell, glo0,
-                              glo1, glo2, gh, nb0, nb1, nb2);
-    if ((threadIdx.x & (LANES - 1)) == 0) {
+      found = slow_find(p, hint ? hint[t] : -1, rec_off, rec, nbr_off, nbr, bb, gb_off, gb_cell, glo0, glo1, glo2, gh, nb0,
+                        nb1, nb2);
+    // the ball about p inside the cell found, when the plane test shows p that far inside; else no ball
+    // until the next record test in this cell
+    float4 ball = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (found >= 0 && pl32) {
+      float4 b;
+      if (plane_ball<32>(p, rec32 + (int64_t)kR32 * found, pl32 + (int64_t)kPl * found, b)) ball = b;
+    }
+    if ((threadIdx.x & 31) == 0) {
       cell_t[t] = found;
-      // the ball about p inside the cell found, when the plane test shows p that far inside; else no ball
-      // until the next record test in this cell
-      float4 ball = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (found >= 0 && pl32) {
-        float4 b;
-        if (plane_ball(p, rec32 + (int64_t)kR32 * found, pl32 + (int64_t)kPl * found, b)) ball = b;
-      }
       ref[i] = ball;
       if (found < 0)
         atomicAdd(status, 1ull);
@@ -587,7 +562,8 @@ __global__ __launch_bounds__(256) void k_locate_slow(
 }
 
 
-// ---- exclusive scan of int32 counts into OutT offsets (out[n] = total)
+// ---- exclusive scans over the cells: occupancy -> cell_start, and occupancy x reaction slots per molecule -> slot_base
+// (HALF: the steps whose FP32 forces take the half lists; otherwise only its total).  out[n] = total.
 
 constexpr int kScanThreads = 1024, kScanItems = 4, kScanTile = kScanThreads * kScanItems;
 
@@ -620,44 +596,94 @@ __device__ OutT block_exclusive_scan(OutT v, OutT *sh, OutT &total) {
   return r;
 }
 
-template <typename InT, typename OutT>
-__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const InT *in, int64_t n, OutT *out, OutT *tile_sum) {
-  __shared__ OutT sh[kScanThreads / 64 + 1];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  OutT v[kScanItems], s = 0;
+// What bounds a small system's binning is its launches (2.5 to 5 us each): both scans are one pass over the cells and,
+// up to kScanDirect cells, one launch.
+// One tile of kScanTile cells; returns the tile's totals and writes the offsets plus c0 / s0.
+template <bool HALF>
+__device__ __forceinline__ void scan_tile(const int32_t *count, const int32_t *rcnt, int64_t n, int64_t tile, int32_t c0,
+                                          int64_t s0, int32_t *cell_start, int64_t *slot_base, int32_t &ctot, int64_t &stot) {
+  __shared__ int32_t shc[kScanThreads / 64 + 1];
+  __shared__ int64_t shs[kScanThreads / 64 + 1];
+  const int64_t base = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  int32_t v[kScanItems], c = 0;
+  int64_t x[kScanItems], sl = 0;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
-    v[k] = base + k < n ? (OutT)in[base + k] : 0;
-    s += v[k];
+    v[k] = base + k < n ? count[base + k] : 0;
+    x[k] = base + k < n ? (int64_t)v[k] * rcnt[base + k] : 0;
+    c += v[k];
+    sl += x[k];
   }
-  OutT total;
-  OutT ex = block_exclusive_scan<OutT>(s, sh, total);
+  int32_t ec = block_exclusive_scan<int32_t>(c, shc, ctot) + c0;
+  int64_t es = block_exclusive_scan<int64_t>(sl, shs, stot) + s0;
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
-    if (base + k < n) out[base + k] = ex;
-    ex += v[k];
+    if (base + k < n) {
+      cell_start[base + k] = ec;
+      if (HALF) slot_base[base + k] = es;
+    }
+    ec += v[k];
+    es += x[k];
   }
-  if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
 }
-
-template <typename OutT>
-__global__ __launch_bounds__(kScanThreads) void k_scan_sums(OutT *tile_sum, int64_t ntiles, OutT *out, int64_t n) {
-  __shared__ OutT sh[kScanThreads / 64 + 1];
-  OutT carry = 0;
+// A few tiles: one block takes them in turn.
+template <bool HALF>
+__global__ __launch_bounds__(kScanThreads) void k_scan_cells(const int32_t *count, const int32_t *rcnt, int64_t n,
+                                                              int32_t *cell_start, int64_t *slot_base,
+                                                              unsigned long long *slots) {
+  int32_t c = 0, ct;
+  int64_t s = 0, st;
+  for (int64_t t = 0; t * kScanTile < n; ++t) {
+    scan_tile<HALF>(count, rcnt, n, t, c, s, cell_start, slot_base, ct, st);
+    c += ct;
+    s += st;
+  }
+  if (threadIdx.x == 0) {
+    cell_start[n] = c;
+    if (HALF) slot_base[n] = s;
+    *slots = (unsigned long long)s;
+  }
+}
+// Many tiles: every tile on its own, the tile totals, then the totals before each tile added.
+template <bool HALF>
+__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const int32_t *count, const int32_t *rcnt, int64_t n,
+                                                              int32_t *cell_start, int64_t *slot_base, int64_t *tile_sum) {
+  int32_t ct;
+  int64_t st;
+  scan_tile<HALF>(count, rcnt, n, blockIdx.x, 0, 0, cell_start, slot_base, ct, st);
+  if (threadIdx.x == 0) {
+    tile_sum[2 * (int64_t)blockIdx.x] = ct;
+    tile_sum[2 * (int64_t)blockIdx.x + 1] = st;
+  }
+}
+template <bool HALF>
+__global__ __launch_bounds__(kScanThreads) void k_scan_sums(int64_t *tile_sum, int64_t ntiles, int64_t n, int32_t *cell_start,
+                                                             int64_t *slot_base, unsigned long long *slots) {
+  __shared__ int64_t sh[kScanThreads / 64 + 1];
+  int64_t carry[2] = {0, 0};
   for (int64_t b = 0; b < ntiles; b += kScanThreads) {
     const int64_t i = b + threadIdx.x;
-    OutT v = i < ntiles ? tile_sum[i] : 0, total;
-    OutT ex = block_exclusive_scan<OutT>(v, sh, total);
-    if (i < ntiles) tile_sum[i] = ex + carry;
-    carry += total;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int64_t v = i < ntiles ? tile_sum[2 * i + k] : 0;
+      int64_t total;
+      const int64_t ex = block_exclusive_scan<int64_t>(v, sh, total);
+      if (i < ntiles) tile_sum[2 * i + k] = ex + carry[k];
+      carry[k] += total;
+    }
   }
-  if (threadIdx.x == 0) out[n] = carry;
+  if (threadIdx.x == 0) {
+    cell_start[n] = (int32_t)carry[0];
+    if (HALF) slot_base[n] = carry[1];
+    *slots = (unsigned long long)carry[1];
+  }
 }
-
-template <typename OutT>
-__global__ void k_scan_add(OutT *out, int64_t n, const OutT *tile_sum) {
+template <bool HALF>
+__global__ void k_scan_add(int64_t n, const int64_t *tile_sum, int32_t *cell_start, int64_t *slot_base) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] += tile_sum[i / kScanTile];
+  if (i >= n) return;
+  cell_start[i] += (int32_t)tile_sum[2 * (i / kScanTile)];
+  if (HALF) slot_base[i] += tile_sum[2 * (i / kScanTile) + 1];
 }
 
 // rank_t[t]: the place the locate kernels' count took for the molecule inside its cell (any order; the cells are
@@ -686,23 +712,11 @@ __global__ void k_sort_cells(const int32_t *__restrict__ cell_start, const int32
   perm[r] = v;
 }
 
-__global__ void k_group_ranges(const int32_t *cell_start, const int32_t *g_cell0, int64_t ng, int32_t *g_start,
-                               int32_t *mol_group) {
-  const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (a > ng) return;
-  const int32_t s = cell_start[g_cell0[a]];
-  g_start[a] = s;
-  if (a < ng) {
-    const int32_t e = cell_start[g_cell0[a + 1]];
-    for (int32_t m = s; m < e; ++m) mol_group[m] = (int32_t)a;
-  }
-}
-
-__global__ void k_entry_counts(const int32_t *e_B, int64_t E, const int32_t *g_start, int32_t *cnt) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= E) return;
-  const int32_t B = e_B[e];
-  cnt[e] = g_start[B + 1] - g_start[B];
+// Cleared at the start of a binning: the cells' occupancies and the status words.
+__global__ void k_clear_bin(int32_t *count, int64_t nc, unsigned long long *status, int nstatus) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < nc) count[i] = 0;
+  if (i < nstatus) status[i] = 0;
 }
 
 template <typename T>
@@ -724,28 +738,6 @@ template <>
 struct Vec4<double> {
   using type = double4;
 };
-
-// Gather positions into cell-sorted order, in group-local coordinates (x - origin of the molecule's
-// group); the species id rides in .w as integer bits.
-template <typename T, typename PT>
-__global__ void k_gather(const PT *__restrict__ pos, const int32_t *__restrict__ species, const int32_t *perm,
-                         const int32_t *mol_group, const double *orig, int64_t n, int nsp,
-                         typename Vec4<T>::type *out) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= n) return;
-  const int32_t id = perm[m];
-  const int32_t a = mol_group[m];
-  typename Vec4<T>::type v;
-  v.x = (T)((double)pos[3 * (int64_t)id] - orig[3 * (int64_t)a]);
-  v.y = (T)((double)pos[3 * (int64_t)id + 1] - orig[3 * (int64_t)a + 1]);
-  v.z = (T)((double)pos[3 * (int64_t)id + 2] - orig[3 * (int64_t)a + 2]);
-  const int32_t t = species ? min(max(species[id], 0), nsp - 1) : 0;  // out-of-range ids are clamped
-  if constexpr (sizeof(T) == 4)
-    v.w = __builtin_bit_cast(float, t);
-  else
-    v.w = __builtin_bit_cast(double, (int64_t)t);
-  out[m] = v;
-}
 
 // Gather by groups, one wave each: positions in cell-sorted order relative to the group's origin (species id in .w as
 // integer bits), and the box of the group's molecules (empty: lo > hi).
@@ -790,6 +782,7 @@ __global__ __launch_bounds__(256) void k_gather_groups(const PT *__restrict__ po
       gout[m] = v;
     }
   }
+  if (!box) return;
 #pragma unroll
   for (int s = 1; s < 64; s <<= 1)
 #pragma unroll
@@ -995,15 +988,27 @@ inline int red_blocks(int64_t ng, int64_t &chunk) {
 
 inline unsigned grid1d(int64_t n, int b) { return (unsigned)std::max<int64_t>(1, (n + b - 1) / b); }
 
-template <typename OutT>
-int scan_exclusive(aica_dil *h, const int32_t *in, int64_t n, OutT *out, hipStream_t st) {
-  const int64_t ntiles = std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile);
-  int rc = h->d_scan_tmp.ensure(sizeof(OutT) * (ntiles + 1));
-  if (rc) return rc;
-  OutT *ts = h->d_scan_tmp.as<OutT>();
-  hipLaunchKernelGGL((k_scan_tiles<int32_t, OutT>), dim3((unsigned)ntiles), dim3(kScanThreads), 0, st, in, n, out, ts);
-  hipLaunchKernelGGL((k_scan_sums<OutT>), dim3(1), dim3(kScanThreads), 0, st, ts, ntiles, out, n);
-  hipLaunchKernelGGL((k_scan_add<OutT>), dim3(grid1d(n, 256)), dim3(256), 0, st, out, n, (const OutT *)ts);
+// cell_start, slot_base (half) and the number of reaction slots from the cells' occupancies.
+constexpr int64_t kScanDirect = 8 * kScanTile;  // up to 32,768 cells one block takes about as long as one launch more
+int scan_cells(aica_dil *h, int64_t nc, bool half, unsigned long long *slots, hipStream_t st) {
+  const int64_t ntiles = std::max<int64_t>(1, (nc + kScanTile - 1) / kScanTile);
+  const int32_t *count = h->d_count.as<int32_t>(), *rcnt = h->d_rcnt.as<int32_t>();
+  int32_t *cs = h->d_cell_start.as<int32_t>();
+  int64_t *sb = h->d_slot_base.as<int64_t>();
+  if (nc <= kScanDirect) {
+    hipLaunchKernelGGL(half ? k_scan_cells<true> : k_scan_cells<false>, dim3(1), dim3(kScanThreads), 0, st, count, rcnt, nc,
+                       cs, sb, slots);
+  } else {
+    int rc = h->d_scan_tmp.ensure(sizeof(int64_t) * 2 * ntiles);
+    if (rc) return rc;
+    int64_t *ts = h->d_scan_tmp.as<int64_t>();
+    hipLaunchKernelGGL(half ? k_scan_tiles<true> : k_scan_tiles<false>, dim3((unsigned)ntiles), dim3(kScanThreads), 0, st,
+                       count, rcnt, nc, cs, sb, ts);
+    hipLaunchKernelGGL(half ? k_scan_sums<true> : k_scan_sums<false>, dim3(1), dim3(kScanThreads), 0, st, ts, ntiles, nc, cs,
+                       sb, slots);
+    hipLaunchKernelGGL(half ? k_scan_add<true> : k_scan_add<false>, dim3(grid1d(nc, 256)), dim3(256), 0, st, nc,
+                       (const int64_t *)ts, cs, sb);
+  }
   HIPCHK(hipGetLastError());
   return AICA_OK;
 }
@@ -1074,7 +1079,7 @@ static int upload_geometry(aica_dil *h) {
     });
     if ((rc = upload(h->d_rec_off, roff))) return rc;
     if ((rc = upload(h->d_rec, rec))) return rc;
-    // FP32 records (layout at surely_in_rec32), when every cell fits the fixed stride
+    // FP32 records (layout at kR32), when every cell fits the fixed stride
     bool fits = true;
     for (int64_t s = 0; s < g.nc && fits; ++s) {
       const double *R = rec.data() + roff[s];
@@ -1407,6 +1412,14 @@ void aica_dil_free(aica_dil *h) {
   delete h;
 }
 
+// Which lists a force call runs on.  The full lists (k_force: every pair from both sides, no reaction records) take
+// FP64, and FP32 from 200,000 molecules on: the channel's 6.7M molecules take 1.65 ms in place of 2.50 ms (pair
+// kernel) and 0.34 ms (finalize), a step (bin, forces, adjoint) of the 219,488-molecule mixture 0.50 ms in place of
+// 0.60.  Below that, and with rotating referral, FP32 keeps the half lists: U and W are sums of FP32 terms whose
+// partial sums round to about 1e-9 of the result at 1e4 to 1e5 molecules (at 4e5 across a rotation, where U and W
+// cancel more), and with the half lists they keep the tile-wise partial sums they had.
+static bool full_lists(const aica_dil *h, int64_t n, int tsize) { return tsize == 8 || (n >= 200000 && !h->geo.has_rot); }
+
 int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, void *hip_stream) {
   if (!h) return fail(AICA_E_INVAL, "handle is NULL");
   h->bin_valid = false;
@@ -1425,15 +1438,16 @@ int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, voi
   }
   rc = ensure_groups(h, n);
   if (rc) return rc;
-  const int64_t nc = h->geo.nc, ng = h->grp.ng, E = h->grp.e_off[ng];
+  const int64_t nc = h->geo.nc;
+  if (!h->host_status && hipHostMalloc((void **)&h->host_status, 8 * (8 + kRouteSlots)) != hipSuccess) {
+    h->host_status = nullptr;
+    return fail(AICA_E_NOMEM, "pinned host allocation failed");
+  }
   if ((rc = h->d_cell_of.ensure(4 * std::max<int64_t>(n, 1)))) return rc;
   if ((rc = h->d_count.ensure(4 * nc))) return rc;
   if ((rc = h->d_cell_start.ensure(4 * (nc + 1)))) return rc;
   if ((rc = h->d_rank.ensure(4 * std::max<int64_t>(n, 1)))) return rc;
   if ((rc = h->d_perm.ensure(4 * std::max<int64_t>(n, 1)))) return rc;
-  if ((rc = h->d_g_start.ensure(4 * (ng + 1)))) return rc;
-  if ((rc = h->d_mol_group.ensure(4 * std::max<int64_t>(n, 1)))) return rc;
-  if ((rc = h->d_jcnt.ensure(4 * std::max<int64_t>(nc, 1)))) return rc;
   if ((rc = h->d_slot_base.ensure(8 * (nc + 1)))) return rc;
   if ((rc = h->d_cell_sorted.ensure(4 * std::max<int64_t>(n, 1)))) return rc;
   if ((rc = h->d_status.ensure(8 * (8 + kRouteSlots)))) return rc;
@@ -1442,12 +1456,11 @@ int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, voi
 
   ProfScope ps(h, "bin", st);
   unsigned long long *status = h->d_status.as<unsigned long long>();
-  // status: [0] unlocated, [1] over-full cells, [2] slow-kernel molecules, [8 ..) counters of the molecules
-  // the records located
-  hipLaunchKernelGGL((k_fill<unsigned long long>), dim3(1), dim3(8 + kRouteSlots), 0, st, status,
-                     (int64_t)(8 + kRouteSlots), 0ull);
+  // status: [0] unlocated, [1] reaction slots, [2] slow-kernel molecules, [8 ..) counters of the molecules the
+  // records located
+  hipLaunchKernelGGL(k_clear_bin, dim3(grid1d(std::max<int64_t>(nc, 8 + kRouteSlots), 256)), dim3(256), 0, st,
+                     h->d_count.as<int32_t>(), nc, status, 8 + kRouteSlots);
   unsigned long long *routes = status + 8;
-  hipLaunchKernelGGL((k_fill<int32_t>), dim3(grid1d(nc, 256)), dim3(256), 0, st, h->d_count.as<int32_t>(), nc, 0);
   // the previous binning of the same n (if any) gives the traversal order and the hints: its
   // permutation moves to d_perm_prev, and d_cell_sorted still holds its cells until rebuilt below
   const bool prev = h->perm_n == n && n > 0;
@@ -1461,15 +1474,13 @@ int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, voi
     const float4 *pl = h->has_rec32 ? h->d_pl32.as<float4>() : nullptr;
     int32_t *slow = h->d_slow.as<int32_t>();
     unsigned long long *nslow = status + 2;
-    // lanes per molecule of the slow kernel: a whole wave, or 16 (four molecules per wave) when the previous
-    // binning sent more molecules down the slow path than the grid below has waves
-    const bool slow16 = prev && h->located[2] > 4 * 2048;
+    const int mpb = n <= kFewMolecules ? kMpbFew : kMpb;
 #define AICA_LOCATE(PT)                                                                                            \
-  hipLaunchKernelGGL((k_locate_fast<PT>), dim3(grid1d(n, 256 * kLocPerLane)), dim3(256), 0, st, (const PT *)pos_dev, \
+  hipLaunchKernelGGL(n <= kFewMolecules ? (k_locate_fast<PT, kMpbFew>) : (k_locate_fast<PT, kMpb>), dim3(grid1d(n, mpb)), \
+                     dim3(256), 0, st, (const PT *)pos_dev, \
                      n, trav, hint, r32, pl, h->d_ref.as<float4>(), h->d_cell_of.as<int32_t>(), h->d_rank.as<int32_t>(), \
                      h->d_count.as<int32_t>(), nslow, slow, routes);                                               \
-  hipLaunchKernelGGL(!prev ? (k_locate_slow<PT, 1>) : slow16 ? (k_locate_slow<PT, 16>) : (k_locate_slow<PT, 64>), \
-                     dim3(std::min<int64_t>(prev ? grid1d(n, 4) : grid1d(n, 256), 2048)), dim3(256), 0, st,        \
+  hipLaunchKernelGGL((k_locate_slow<PT>), dim3(std::min<int64_t>(grid1d(n, 8), 2048)), dim3(256), 0, st,            \
                      (const PT *)pos_dev, nslow, slow, trav, hint, r32, pl, h->d_rec_off.as<int64_t>(),          \
                      h->d_rec.as<double>(), h->d_nbr_off.as<int64_t>(),                                            \
                      h->d_nbr.as<int32_t>(), h->d_bb.as<double>(), h->d_gb_off.as<int64_t>(),                       \
@@ -1486,7 +1497,7 @@ int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, voi
   }
   // the unlocated count is read with the other counts below (one synchronisation per binning); an
   // unlocated molecule is left out of the occupancy and of the permutation
-  if ((rc = scan_exclusive<int32_t>(h, h->d_count.as<int32_t>(), nc, h->d_cell_start.as<int32_t>(), st))) return rc;
+  if ((rc = scan_cells(h, nc, !full_lists(h, n, 4), status + 1, st))) return rc;
   if (n > 0) {
     // the slow list is done with: its space takes the unsorted molecules
     hipLaunchKernelGGL(k_scatter, dim3(grid1d(n, 256)), dim3(256), 0, st, h->d_cell_of.as<int32_t>(), trav, n,
@@ -1495,17 +1506,12 @@ int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, voi
     hipLaunchKernelGGL(k_sort_cells, dim3(grid1d(n, 256)), dim3(256), 0, st, h->d_cell_start.as<int32_t>(),
                        h->d_cell_sorted.as<int32_t>(), h->d_slow.as<int32_t>(), nc, n, h->d_perm.as<int32_t>());
   }
-  hipLaunchKernelGGL(k_group_ranges, dim3(grid1d(ng + 1, 256)), dim3(256), 0, st, h->d_cell_start.as<int32_t>(),
-                     h->d_g_cell0.as<int32_t>(), ng, h->d_g_start.as<int32_t>(), h->d_mol_group.as<int32_t>());
-  hipLaunchKernelGGL(k_slot_counts, dim3(grid1d(nc, 256)), dim3(256), 0, st, h->d_count.as<int32_t>(),
-                     h->d_rcnt.as<int32_t>(), nc, h->d_jcnt.as<int32_t>());
   HIPCHK(hipGetLastError());
-  if ((rc = scan_exclusive<int64_t>(h, h->d_jcnt.as<int32_t>(), nc, h->d_slot_base.as<int64_t>(), st))) return rc;
-  int64_t jt = 0;
-  unsigned long long stat[8 + kRouteSlots];
-  HIPCHK(hipMemcpyAsync(&jt, h->d_slot_base.as<int64_t>() + nc, 8, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(stat, status, sizeof stat, hipMemcpyDeviceToHost, st));
+  // the counts come back through pinned memory of the handle, in one copy
+  unsigned long long *stat = h->host_status;
+  HIPCHK(hipMemcpyAsync(stat, status, 8 * (8 + kRouteSlots), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
+  const int64_t jt = (int64_t)stat[1];
   const unsigned long long unl = stat[0];
   if (unl > 0) return fail(AICA_E_UNLOCATED, std::to_string(unl) + " molecule(s) lie in no mesh cell");
   h->located[1] = 0;
@@ -1568,13 +1574,6 @@ struct ForceWs {
   uint32_t epoch = 0;
 };
 
-// Which lists a force call runs on.  The full lists (k_force: every pair from both sides, no reaction records) take
-// FP64, and FP32 from 200,000 molecules on: the channel's 6.7M molecules take 1.65 ms in place of 2.50 ms (pair
-// kernel) and 0.34 ms (finalize), a step (bin, forces, adjoint) of the 219,488-molecule mixture 0.50 ms in place of
-// 0.60.  Below that, and with rotating referral, FP32 keeps the half lists: U and W are sums of FP32 terms whose
-// partial sums round to about 1e-9 of the result at 1e4 to 1e5 molecules (at 4e5 across a rotation, where U and W
-// cancel more), and with the half lists they keep the tile-wise partial sums they had.
-static bool full_lists(const aica_dil *h, int tsize) { return tsize == 8 || (h->n >= 200000 && !h->geo.has_rot); }
 
 // Reaction buffer: (re)allocate, fill with a pattern no epoch can equal, and advance the epoch.
 static int prepare_jpart(aica_dil *h, size_t bytes, hipStream_t st) {
@@ -1624,7 +1623,7 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
   const int nsp = tab.nsp;
 #define AICA_LAUNCH_S(MIX, COMP, ROT, SPLIT)                                                                       \
   hipLaunchKernelGGL((k_pair<T, MIX, MODE, COMP, ROT, SPLIT>), dim3((unsigned)padded), dim3(64 * NW), 0, st, pos,         \
-                     h->d_g_start.as<int32_t>(), h->d_g_cell0.as<int32_t>(), h->d_cell_start.as<int32_t>(), ev,    \
+                     h->d_g_cell0.as<int32_t>(), h->d_cell_start.as<int32_t>(), ev,                                        \
                      h->d_slot_base.as<int64_t>(), h->d_nl_off.as<int64_t>(), h->d_nl_e.as<int32_t>(),            \
                      h->d_nl_d.as<int32_t>(), h->d_nl_r.as<int32_t>(), jpart, own, gpart, gnp, ng, padded, tab,     \
                      rot, evd, h->d_perm.as<int32_t>(), cap, pairs_out, pcount, mol_count, ws.epoch)
@@ -1754,41 +1753,19 @@ static void launch_finalize(aica_dil *h, const ForceWs &ws, void *out, hipStream
                      ws.epoch);
 }
 
-// Gather the binned positions into cell-sorted SoA (half lists) at dst ([n] V4 of the compute type).
+// Gather the binned positions by groups (one wave each) into pos: the half lists' groups, or the full lists' with their
+// boxes into box (and G into gsort).
 template <typename T>
-static int gather_to(aica_dil *h, const void *pos_dev, const int32_t *species, int tab_nsp, hipStream_t st, void *dst) {
+static int gather(aica_dil *h, bool full, const void *pos_dev, const int32_t *species, int nsp, hipStream_t st, void *pos,
+                  void *box, const void *G = nullptr, void *gsort = nullptr) {
   using V4 = typename Vec4<T>::type;
-  const int64_t n = h->n;
-  if (n == 0) return AICA_OK;
-  if (h->bin_dtype == AICA_FP64)
-    hipLaunchKernelGGL((k_gather<T, double>), dim3(grid1d(n, 256)), dim3(256), 0, st, (const double *)pos_dev, species,
-                       h->d_perm.as<int32_t>(), h->d_mol_group.as<int32_t>(), h->d_orig.as<double>(), n, tab_nsp, (V4 *)dst);
-  else
-    hipLaunchKernelGGL((k_gather<T, float>), dim3(grid1d(n, 256)), dim3(256), 0, st, (const float *)pos_dev, species,
-                       h->d_perm.as<int32_t>(), h->d_mol_group.as<int32_t>(), h->d_orig.as<double>(), n, tab_nsp, (V4 *)dst);
-  HIPCHK(hipGetLastError());
-  return AICA_OK;
-}
-
-// Gather into the handle's own position buffer (grown as needed).
-template <typename T>
-static int gather(aica_dil *h, const void *pos_dev, const int32_t *species, int tab_nsp, hipStream_t st) {
-  using V4 = typename Vec4<T>::type;
-  int rc = h->d_pos.ensure(sizeof(V4) * std::max<int64_t>(h->n, 1));
-  if (rc) return rc;
-  return gather_to<T>(h, pos_dev, species, tab_nsp, st, h->d_pos.p);
-}
-
-// Gather the binned positions by the groups of the full lists into pos, and their boxes into box.
-template <typename T>
-static int gather_groups(aica_dil *h, const void *pos_dev, const int32_t *species, int nsp, hipStream_t st, void *pos,
-                         void *box, const void *G = nullptr, void *gsort = nullptr) {
-  using V4 = typename Vec4<T>::type;
-  const int64_t ng = h->nb.ng;
+  const int64_t ng = full ? h->nb.ng : h->grp.ng;
+  const int32_t *cell0 = full ? h->d_nb_cell0.as<int32_t>() : h->d_g_cell0.as<int32_t>();
+  const double *orig = full ? h->d_nb_orig.as<double>() : h->d_orig.as<double>();
 #define AICA_GATHER(PT)                                                                                               \
   hipLaunchKernelGGL((k_gather_groups<T, PT>), dim3(grid1d(ng, 4)), dim3(256), 0, st, (const PT *)pos_dev, species,   \
-                     h->d_perm.as<int32_t>(), h->d_cell_start.as<int32_t>(), h->d_nb_cell0.as<int32_t>(),             \
-                     h->d_nb_orig.as<double>(), ng, nsp, (V4 *)pos, (T *)box, (const T *)G, (V4 *)gsort)
+                     h->d_perm.as<int32_t>(), h->d_cell_start.as<int32_t>(), cell0, orig, ng, nsp, (V4 *)pos,         \
+                     (T *)box, (const T *)G, (V4 *)gsort)
   if (h->bin_dtype == AICA_FP64) AICA_GATHER(double);
   else AICA_GATHER(float);
 #undef AICA_GATHER
@@ -1796,11 +1773,19 @@ static int gather_groups(aica_dil *h, const void *pos_dev, const int32_t *specie
   return AICA_OK;
 }
 
+// Positions for pair export and counts, in the handle's buffer (these make no records and need no slot_base).
+template <typename T>
+static int gather_half(aica_dil *h, const void *pos_dev, hipStream_t st) {
+  int rc = h->d_pos.ensure(sizeof(typename Vec4<T>::type) * std::max<int64_t>(h->n, 1));
+  if (rc) return rc;
+  return gather<T>(h, false, pos_dev, nullptr, 1, st, h->d_pos.p, nullptr);
+}
+
 // The handle's grow-only workspace for a force call (allocating on first use or growth).
 template <typename T>
 static int handle_ws(aica_dil *h, ForceWs &ws, hipStream_t st) {
   using V4 = typename Vec4<T>::type;
-  const bool full = full_lists(h, sizeof(T));
+  const bool full = full_lists(h, h->n, sizeof(T));
   const int64_t n = h->n, ng = full ? h->nb.ng : h->grp.ng;
   int rc;
   if ((rc = h->d_pos.ensure(sizeof(V4) * std::max<int64_t>(n, 1)))) return rc;
@@ -1836,7 +1821,7 @@ template <typename T>
 static int forces_impl(aica_dil *h, const ForceWs &ws, const void *pos_dev, const int32_t *species, const LJTab &tab,
                        bool comp, void *forces_dev, double *uw_dev, int64_t *npairs_dev, hipStream_t st,
                        bool prof = true) {
-  const bool full = full_lists(h, sizeof(T));
+  const bool full = full_lists(h, h->n, sizeof(T));
   const int64_t n = h->n, ng = full ? h->nb.ng : h->grp.ng;
   int rc;
   const bool was = h->profiling;
@@ -1846,9 +1831,7 @@ static int forces_impl(aica_dil *h, const ForceWs &ws, const void *pos_dev, cons
     bool v;
     ~Restore() { h->profiling = v; }
   } restore{h, was};
-  rc = full ? gather_groups<T>(h, pos_dev, species, tab.nsp, st, ws.pos, ws.box)
-            : gather_to<T>(h, pos_dev, species, tab.nsp, st, ws.pos);
-  if (rc) return rc;
+  if ((rc = gather<T>(h, full, pos_dev, species, tab.nsp, st, ws.pos, full ? ws.box : nullptr))) return rc;
   {
     ProfScope ps(h, "pair_fwd", st);
     if (full) {
@@ -1933,7 +1916,7 @@ template <typename T>
 static int forces_noalloc(aica_dil *h, const void *pos_dev, const int32_t *species, const LJTab &tab, bool comp,
                           void *forces_dev, double *uw_dev, int64_t *npairs_dev, hipStream_t st) {
   using V4 = typename Vec4<T>::type;
-  const bool full = full_lists(h, sizeof(T));
+  const bool full = full_lists(h, h->n, sizeof(T));
   const int64_t n = h->n, ng = full ? h->nb.ng : h->grp.ng, J = h->jtotal;
   const size_t b_pos = align256(sizeof(V4) * std::max<int64_t>(n, 1));
   const size_t b_own = align256(sizeof(T) * 8 * std::max<int64_t>(n, 1));
@@ -1996,12 +1979,12 @@ int aica_pairs_export(aica_dil *h, const void *pos_dev, const aica_params *param
   unsigned long long *pc = h->d_pcount.as<unsigned long long>();
   hipLaunchKernelGGL((k_fill<unsigned long long>), dim3(1), dim3(64), 0, st, pc, (int64_t)1, 0ull);
   if (params->precision == AICA_FP32) {
-    if ((rc = gather<float>(h, pos_dev, nullptr, 1, st))) return rc;
+    if ((rc = gather_half<float>(h, pos_dev, st))) return rc;
     ForceWs ws;
     ws.pos = h->d_pos.p;
     if ((rc = launch_pair<float, 1>(h, ws, tab, false, st, cap, pc))) return rc;
   } else {
-    if ((rc = gather<double>(h, pos_dev, nullptr, 1, st))) return rc;
+    if ((rc = gather_half<double>(h, pos_dev, st))) return rc;
     ForceWs ws;
     ws.pos = h->d_pos.p;
     if ((rc = launch_pair<double, 1>(h, ws, tab, false, st, cap, pc))) return rc;
@@ -2049,12 +2032,12 @@ int aica_pair_counts(aica_dil *h, const void *pos_dev, const aica_params *params
   if (h->n == 0) return AICA_OK;
   hipLaunchKernelGGL((k_fill<int32_t>), dim3(grid1d(h->n, 256)), dim3(256), 0, st, counts_dev, h->n, 0);
   if (params->precision == AICA_FP32) {
-    if ((rc = gather<float>(h, pos_dev, nullptr, 1, st))) return rc;
+    if ((rc = gather_half<float>(h, pos_dev, st))) return rc;
     ForceWs ws;
     ws.pos = h->d_pos.p;
     if ((rc = launch_pair<float, 1>(h, ws, tab, false, st, -1, nullptr, counts_dev))) return rc;
   } else {
-    if ((rc = gather<double>(h, pos_dev, nullptr, 1, st))) return rc;
+    if ((rc = gather_half<double>(h, pos_dev, st))) return rc;
     ForceWs ws;
     ws.pos = h->d_pos.p;
     if ((rc = launch_pair<double, 1>(h, ws, tab, false, st, -1, nullptr, counts_dev))) return rc;
