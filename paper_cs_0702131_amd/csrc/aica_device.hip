@@ -104,8 +104,7 @@ struct aica_dil {
   double glo[3] = {0, 0, 0}, gh = 1;
   int64_t gnb[3] = {1, 1, 1};
   // interaction groups (depend on the number density; built on the first aica_bin)
-  bool groups_ready = false;
-  int64_t groups_for_n = -1;
+  bool groups_ready = false, neigh_ready = false;
   Groups grp;
   DBuf d_orig, d_g_cell0, d_e_off, d_e_B, d_e_vec32, d_e_vec64, d_nl_off, d_nl_e, d_nl_d, d_nl_r, d_rcnt;
   // full neighbour lists of the force kernel (its own groups; same lifetime)
@@ -1232,12 +1231,9 @@ static int upload_geometry(aica_dil *h) {
   return AICA_OK;
 }
 
-static int ensure_groups(aica_dil *h, int64_t n) {
-  if (h->groups_ready && h->groups_for_n == n) return AICA_OK;
-  auto t0 = std::chrono::steady_clock::now();
-  const double density = (double)n / h->geo.total_volume;
-  double target = 64.0;  // largest expected occupancy of a group (k-d subtree; measured best on the channel)
-  if (const char *e = getenv("AICA_GROUP_TARGET")) target = std::max(1.0, atof(e));
+// The half lists' groups and lists for a number density.
+static int make_groups(aica_dil *h, double density, double target) {
+  h->groups_ready = false;
   int rc = build_groups(h->geo, h->order, h->split_depth, h->pairs, density, target, h->grp);
   if (rc) return rc;
   const Groups &G = h->grp;
@@ -1247,23 +1243,25 @@ static int ensure_groups(aica_dil *h, int64_t n) {
   // Entry offsets: a j of group B at xm relative to orig_B is referred into A's frame at R xm + o with
   // o = T(orig_B) - orig_A (R = I and o = orig_B + t - orig_A for a translation).  The fourth component
   // holds the image code, plus kRotFlag when the image has a rotation (whose R the kernels look up).
-  for (int64_t e = 0; e < E; ++e) {
-    const int64_t B = G.e_B[e];
-    int64_t A = std::upper_bound(G.e_off.begin(), G.e_off.end(), e) - G.e_off.begin() - 1;
-    const Xf T = image_transform(h->geo, G.e_img[3 * e], G.e_img[3 * e + 1], G.e_img[3 * e + 2]);
-    double o[3];
-    if (T.rot) {
-      double tb[3];
-      T.apply(&G.orig[3 * B], tb);
-      for (int q = 0; q < 3; ++q) o[q] = tb[q] - G.orig[3 * A + q];
-    } else {
-      for (int q = 0; q < 3; ++q) o[q] = G.orig[3 * B + q] + T.y[q] - G.orig[3 * A + q];
-    }
-    const int code = 9 * (G.e_img[3 * e] + 1) + 3 * (G.e_img[3 * e + 1] + 1) + (G.e_img[3 * e + 2] + 1) +
-                     (T.rot ? kRotFlag : 0);
-    v32[e] = make_float4((float)o[0], (float)o[1], (float)o[2], __builtin_bit_cast(float, code));
-    v64[e] = make_double4(o[0], o[1], o[2], __builtin_bit_cast(double, (int64_t)code));
-  }
+  parallel_for(G.ng, [&](int64_t b, int64_t en, int) {
+    for (int64_t A = b; A < en; ++A)
+      for (int64_t e = G.e_off[A]; e < G.e_off[A + 1]; ++e) {
+        const int64_t B = G.e_B[e];
+        const Xf T = image_transform(h->geo, G.e_img[3 * e], G.e_img[3 * e + 1], G.e_img[3 * e + 2]);
+        double o[3];
+        if (T.rot) {
+          double tb[3];
+          T.apply(&G.orig[3 * B], tb);
+          for (int q = 0; q < 3; ++q) o[q] = tb[q] - G.orig[3 * A + q];
+        } else {
+          for (int q = 0; q < 3; ++q) o[q] = G.orig[3 * B + q] + T.y[q] - G.orig[3 * A + q];
+        }
+        const int code = 9 * (G.e_img[3 * e] + 1) + 3 * (G.e_img[3 * e + 1] + 1) + (G.e_img[3 * e + 2] + 1) +
+                         (T.rot ? kRotFlag : 0);
+        v32[e] = make_float4((float)o[0], (float)o[1], (float)o[2], __builtin_bit_cast(float, code));
+        v64[e] = make_double4(o[0], o[1], o[2], __builtin_bit_cast(double, (int64_t)code));
+      }
+  });
   if (h->geo.has_rot) {  // R of every image code (the identity for translations)
     std::vector<double> r64(27 * 9);
     for (int code = 0; code < 27; ++code) {
@@ -1289,70 +1287,90 @@ static int ensure_groups(aica_dil *h, int64_t n) {
     if ((rc = upload(h->d_rcnt, rcnt))) return rc;
   }
   if ((rc = upload(h->d_orig, G.orig))) return rc;
-  // the force kernel's neighbour lists
+  h->groups_ready = true;
+  return AICA_OK;
+}
+
+// The full lists' groups and lists.
+static int make_neigh(aica_dil *h, double density, double target) {
+  h->neigh_ready = false;
+  int rc = build_neigh(h->geo, h->order, h->split_depth, h->pairs, h->predicate == AICA_DIL_VERTEX, density, target, h->nb);
+  if (rc) return rc;
+  const Neigh &N = h->nb;
+  const int64_t NE = N.e_off[N.ng];
+  std::vector<float4> v32(NE);
+  std::vector<double4> v64(NE);
+  parallel_for(N.ng, [&](int64_t b, int64_t e, int) {
+    for (int64_t a = b; a < e; ++a)
+      for (int64_t k = N.e_off[a]; k < N.e_off[a + 1]; ++k) {
+        const int64_t B = N.e_B[k];
+        const int c = N.e_code[k];
+        const Xf T = image_transform(h->geo, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
+        double o[3], tb[3] = {0, 0, 0};
+        if (T.rot) T.apply(&N.orig[3 * B], tb);
+        for (int q = 0; q < 3; ++q)
+          o[q] = T.rot ? tb[q] - N.orig[3 * a + q] : N.orig[3 * B + q] + T.y[q] - N.orig[3 * a + q];
+        const int code = c + (T.rot ? kRotFlag : 0);
+        v32[k] = make_float4((float)o[0], (float)o[1], (float)o[2], __builtin_bit_cast(float, code));
+        v64[k] = make_double4(o[0], o[1], o[2], __builtin_bit_cast(double, (int64_t)code));
+      }
+  });
+  if (h->geo.has_rot) {
+    std::vector<int32_t> list, turned;
+    for (int64_t a = 0; a < N.ng; ++a) {
+      bool rot = false;
+      for (int64_t e = N.e_off[a]; e < N.e_off[a + 1] && !rot; ++e) {
+        const int c = N.e_code[e];
+        rot = image_transform(h->geo, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1).rot;
+      }
+      (rot ? turned : list).push_back((int32_t)a);
+    }
+    h->nb_plain_groups = (int64_t)list.size();
+    list.insert(list.end(), turned.begin(), turned.end());
+    if ((rc = upload(h->d_nb_glist, list))) return rc;
+  }
+  if ((rc = upload(h->d_nb_cell0, N.cell0))) return rc;
+  if ((rc = upload(h->d_nb_run_off, N.run_off))) return rc;
+  if ((rc = upload(h->d_nb_runs, N.runs))) return rc;
+  if ((rc = upload(h->d_nb_eB, N.e_B))) return rc;
+  if ((rc = upload(h->d_nb_eoff, N.e_off))) return rc;
+  if ((rc = upload(h->d_nb_erev, N.e_rev))) return rc;
+  if ((rc = upload(h->d_nb_vec32, v32))) return rc;
+  if ((rc = upload(h->d_nb_vec64, v64))) return rc;
+  if ((rc = upload(h->d_nb_orig, N.orig))) return rc;
+  if (getenv("AICA_VERBOSE"))
+    fprintf(stderr, "neighbour lists: %lld groups, %lld entries, %lld runs, reach %.3f\n", (long long)N.ng, (long long)NE,
+            (long long)N.runs.size(), N.reach);
+  if (getenv("AICA_VERBOSE")) {
+    double vol = 0, cells = 0;
+    for (const CellRun &r : N.runs)
+      for (int32_t s = r.d0; s < r.d1; ++s) {
+        vol += h->geo.vol[h->order[s]];
+        cells += 1;
+      }
+    fprintf(stderr, "neighbour lists: per group %.1f runs, %.1f cells, %.1f molecules expected\n", (double)N.runs.size() / N.ng,
+            cells / N.ng, vol * density / N.ng);
+  }
+  h->neigh_ready = true;
+  return AICA_OK;
+}
+
+// Both sets of lists, for n molecules.  They are kept while n leaves the cuts as they are: a program whose molecule
+// count changes from step to step rebuilt them at every binning (117 ms of host work at 371,896 molecules, 1.6 s at 6.7
+// million).
+static int ensure_groups(aica_dil *h, int64_t n) {
+  const double density = (double)n / h->geo.total_volume;
+  double target = 64.0;  // largest expected occupancy of a group (k-d subtree; measured best on the channel)
+  if (const char *e = getenv("AICA_GROUP_TARGET")) target = std::max(1.0, atof(e));
   double nb_target = 128.0;
   if (const char *e = getenv("AICA_NB_TARGET")) nb_target = std::max(1.0, atof(e));
-  if ((rc = build_neigh(h->geo, h->order, h->split_depth, h->pairs, h->predicate == AICA_DIL_VERTEX, density, nb_target, h->nb)))
-    return rc;
-  {
-    const Neigh &N = h->nb;
-    const int64_t NE = N.e_off[N.ng];
-    v32.resize(NE);
-    v64.resize(NE);
-    parallel_for(N.ng, [&](int64_t b, int64_t e, int) {
-      for (int64_t a = b; a < e; ++a)
-        for (int64_t k = N.e_off[a]; k < N.e_off[a + 1]; ++k) {
-          const int64_t B = N.e_B[k];
-          const int c = N.e_code[k];
-          const Xf T = image_transform(h->geo, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
-          double o[3], tb[3] = {0, 0, 0};
-          if (T.rot) T.apply(&N.orig[3 * B], tb);
-          for (int q = 0; q < 3; ++q)
-            o[q] = T.rot ? tb[q] - N.orig[3 * a + q] : N.orig[3 * B + q] + T.y[q] - N.orig[3 * a + q];
-          const int code = c + (T.rot ? kRotFlag : 0);
-          v32[k] = make_float4((float)o[0], (float)o[1], (float)o[2], __builtin_bit_cast(float, code));
-          v64[k] = make_double4(o[0], o[1], o[2], __builtin_bit_cast(double, (int64_t)code));
-        }
-    });
-    if (h->geo.has_rot) {
-      std::vector<int32_t> list, turned;
-      for (int64_t a = 0; a < N.ng; ++a) {
-        bool rot = false;
-        for (int64_t e = N.e_off[a]; e < N.e_off[a + 1] && !rot; ++e) {
-          const int c = N.e_code[e];
-          rot = image_transform(h->geo, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1).rot;
-        }
-        (rot ? turned : list).push_back((int32_t)a);
-      }
-      h->nb_plain_groups = (int64_t)list.size();
-      list.insert(list.end(), turned.begin(), turned.end());
-      if ((rc = upload(h->d_nb_glist, list))) return rc;
-    }
-    if ((rc = upload(h->d_nb_cell0, N.cell0))) return rc;
-    if ((rc = upload(h->d_nb_run_off, N.run_off))) return rc;
-    if ((rc = upload(h->d_nb_runs, N.runs))) return rc;
-    if ((rc = upload(h->d_nb_eB, N.e_B))) return rc;
-    if ((rc = upload(h->d_nb_eoff, N.e_off))) return rc;
-    if ((rc = upload(h->d_nb_erev, N.e_rev))) return rc;
-    if ((rc = upload(h->d_nb_vec32, v32))) return rc;
-    if ((rc = upload(h->d_nb_vec64, v64))) return rc;
-    if ((rc = upload(h->d_nb_orig, N.orig))) return rc;
-    if (getenv("AICA_VERBOSE"))
-      fprintf(stderr, "neighbour lists: %lld groups, %lld entries, %lld runs, reach %.3f\n", (long long)N.ng, (long long)NE,
-              (long long)N.runs.size(), N.reach);
-    if (getenv("AICA_VERBOSE")) {
-      double vol = 0, cells = 0;
-      for (const CellRun &r : N.runs)
-        for (int32_t s = r.d0; s < r.d1; ++s) {
-          vol += h->geo.vol[h->order[s]];
-          cells += 1;
-        }
-      fprintf(stderr, "neighbour lists: per group %.1f runs, %.1f cells, %.1f molecules expected\n", (double)N.runs.size() / N.ng,
-              cells / N.ng, vol * density / N.ng);
-    }
-  }
-  h->groups_ready = true;
-  h->groups_for_n = n;
+  const bool keep = h->groups_ready && h->grp.cut.holds(density, target);
+  const bool nb_keep = h->neigh_ready && h->nb.cut.holds(density, nb_target);
+  if (keep && nb_keep) return AICA_OK;
+  auto t0 = std::chrono::steady_clock::now();
+  int rc;
+  if (!keep && (rc = make_groups(h, density, target))) return rc;
+  if (!nb_keep && (rc = make_neigh(h, density, nb_target))) return rc;
   h->group_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   return AICA_OK;
 }

@@ -110,9 +110,20 @@ struct CellPair {
 int build_cell_pairs(const Geometry &g, const std::vector<int32_t> &order, const std::vector<int32_t> &rank,
                      double R, int predicate, std::vector<CellPair> &out);
 
+// Which number densities cut the k-d tree into the same groups: a node is split when density * volume > target, so
+// the cut stays while that holds for the smallest node split and not for the largest node of several cells left whole.
+// The lists depend on the density by the cut alone.
+struct GroupCut {
+  double target = -1, split_vol = 0, whole_vol = 0;  // split_vol < 0: nothing was split; target < 0: no lists
+  bool holds(double density, double t) const {
+    return t == target && (split_vol < 0 || density * split_vol > t) && !(density * whole_vol > t);
+  }
+};
+
 // Interaction groups: consecutive sorted cells packed to an expected occupancy target.
 struct Groups {
   int64_t ng = 0;
+  GroupCut cut;
   std::vector<int32_t> cell0;   // [ng+1] first sorted cell of each group
   std::vector<int32_t> of_cell; // [nc] group of each sorted cell
   std::vector<double> orig;     // [ng][3] group origin (multiple of 2^-15)
@@ -120,17 +131,13 @@ struct Groups {
   std::vector<int64_t> e_off;   // [ng+1]
   std::vector<int32_t> e_B;     // j-group
   std::vector<int8_t> e_img;    // [E][3] lattice multiples
-  std::vector<int64_t> r_off;   // [ng+1] reverse list: entries whose j-group is B
-  std::vector<int32_t> r_e;     // entry ids
   // needed j-cells: for every non-self entry e = (A, B, t), the cells d of B with some cell of A in
   // range of d + t (CSR by the i-group A, sorted by (e, d))
   std::vector<int64_t> nl_off;  // [ng+1]
   std::vector<int32_t> nl_e;    // entry id
   std::vector<int32_t> nl_d;    // sorted cell id (in group B)
   std::vector<int32_t> nl_r;    // 1 + rank of the entry in the cell's reverse list (0 is the self entry)
-  // reverse of the needed lists by cell: entries whose needed list holds cell d
-  std::vector<int64_t> rc_off;  // [nc+1]
-  std::vector<int32_t> rc_e;
+  std::vector<int64_t> rc_off;  // [nc+1] offsets of the entries whose needed list holds cell d
 };
 
 int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
@@ -146,6 +153,7 @@ struct CellRun {
 // its own group.
 struct Neigh {
   int64_t ng = 0;
+  GroupCut cut;
   std::vector<int32_t> cell0;    // [ng+1] first sorted cell of each group
   std::vector<double> orig;      // [ng][3] group origin (multiple of 2^-15)
   std::vector<int64_t> e_off;    // [ng+1] entries (j-group, image) of each group, without the group itself

@@ -810,9 +810,11 @@ int build_cell_pairs(const Geometry &g, const std::vector<int32_t> &order, const
 // ------------------------------------------------------------------ interaction groups
 
 static void cut_groups(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
-                       double density, double target, std::vector<int32_t> &cell0) {
+                       double density, double target, std::vector<int32_t> &cell0, GroupCut &cut) {
   const int64_t nc = g.nc;
   cell0.clear();
+  cut = GroupCut();
+  double split_vol = -1, whole_vol = 0;
   // Groups are subtrees of the k-d tree of the sorted order: descending from the root, a subtree whose
   // expected occupancy is at most the target becomes a group, so every group is a compact box-like block
   // of cells (a run of the sorted order cut at arbitrary places would straddle subtrees and spread out).
@@ -827,23 +829,29 @@ static void cut_groups(const Geometry &g, const std::vector<int32_t> &order, con
     const Node r = stack.back();
     stack.pop_back();
     if (r.e <= r.b) continue;
-    if (r.e - r.b == 1 || density * (vpre[r.e] - vpre[r.b]) <= target) {
+    const double vol = vpre[r.e] - vpre[r.b];
+    if (r.e - r.b == 1 || density * vol <= target) {
       cell0.push_back((int32_t)r.b);
+      if (r.e - r.b > 1) whole_vol = std::max(whole_vol, vol);
       continue;
     }
+    split_vol = split_vol < 0 ? vol : std::min(split_vol, vol);
     int64_t mid = r.b + 1;
     while (mid < r.e && split_depth[mid] != (uint8_t)std::min(r.depth, 254)) ++mid;
     if (mid >= r.e) mid = r.b + (r.e - r.b) / 2;  // (not reached: every inner node has its split)
     stack.push_back({mid, r.e, r.depth + 1});
     stack.push_back({r.b, mid, r.depth + 1});
   }
+  cut.target = target;
+  cut.split_vol = split_vol;
+  cut.whole_vol = whole_vol;
 }
 
 int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
                  const std::vector<CellPair> &pairs, double density, double target, Groups &G) {
   const int64_t nc = g.nc;
   G.of_cell.assign(nc, 0);
-  cut_groups(g, order, split_depth, density, target, G.cell0);
+  cut_groups(g, order, split_depth, density, target, G.cell0, G.cut);
   for (size_t k = 0; k < G.cell0.size(); ++k) {
     const int64_t e = k + 1 < G.cell0.size() ? G.cell0[k + 1] : nc;
     for (int64_t s = G.cell0[k]; s < e; ++s) G.of_cell[s] = (int32_t)k;
@@ -893,7 +901,6 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
   const int64_t E = G.e_off[ng];
   G.e_B.assign(E, 0);
   G.e_img.assign(3 * E, 0);
-  std::vector<int64_t> rcnt(ng + 1, 0);
   for (int64_t a = 0; a < ng; ++a) {
     int64_t e = G.e_off[a];
     for (int64_t key : lists[a]) {
@@ -903,17 +910,10 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
       G.e_img[3 * e] = (int8_t)(code / 9 - 1);
       G.e_img[3 * e + 1] = (int8_t)((code / 3) % 3 - 1);
       G.e_img[3 * e + 2] = (int8_t)(code % 3 - 1);
-      rcnt[B + 1]++;
       ++e;
     }
     std::vector<int64_t>().swap(lists[a]);
   }
-  for (int64_t b = 0; b < ng; ++b) rcnt[b + 1] += rcnt[b];
-  G.r_off = rcnt;
-  G.r_e.assign(E, 0);
-  std::vector<int64_t> fill(G.r_off.begin(), G.r_off.end() - 1);
-  for (int64_t e = 0; e < E; ++e) G.r_e[fill[G.e_B[e]]++] = (int32_t)e;
-
   // needed j-cells of every non-self entry.  A cell pair (sc, sd, img), sc <= sd, is the physical
   // pair {cell sc, cell sd + img}; in group terms it is evaluated by entry (A, B, img) with j in sd,
   // or, for A == B and a negative image, by entry (A, A, -img) with j in sc.
@@ -968,13 +968,11 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
     std::vector<int64_t>().swap(nlists[a]);
   }
   for (int64_t c = 0; c < nc; ++c) G.rc_off[c + 1] += G.rc_off[c];
-  G.rc_e.assign(NL, 0);
   G.nl_r.assign(NL, 0);
   std::vector<int64_t> cfill(G.rc_off.begin(), G.rc_off.end() - 1);
   for (int64_t k = 0; k < NL; ++k) {
     const int32_t d = G.nl_d[k];
-    G.nl_r[k] = (int32_t)(1 + cfill[d] - G.rc_off[d]);
-    G.rc_e[cfill[d]++] = G.nl_e[k];
+    G.nl_r[k] = (int32_t)(1 + cfill[d]++ - G.rc_off[d]);
   }
   return AICA_OK;
 }
@@ -986,7 +984,7 @@ static constexpr int32_t kRunGap = 2;
 int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
                 const std::vector<CellPair> &pairs, bool whole_groups, double density, double target, Neigh &N) {
   const int64_t nc = g.nc;
-  cut_groups(g, order, split_depth, density, target, N.cell0);
+  cut_groups(g, order, split_depth, density, target, N.cell0, N.cut);
   const int64_t ng = N.ng = (int64_t)N.cell0.size();
   N.cell0.push_back((int32_t)nc);
   std::vector<int32_t> of_cell(nc);
@@ -1130,19 +1128,21 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
       }
     }
   });
+  std::vector<double> far(ext);
+  parallel_for(ng, [&](int64_t b, int64_t e, int) {
+    for (int64_t a = b; a < e; ++a)
+      for (int64_t k = N.e_off[a]; k < N.e_off[a + 1]; ++k) {
+        const int code = N.e_code[k];
+        const Xf T = image_transform(g, code / 9 - 1, (code / 3) % 3 - 1, code % 3 - 1);
+        double tb[3];
+        T.apply(&N.orig[3 * (int64_t)N.e_B[k]], tb);
+        double m = 0;
+        for (int q = 0; q < 3; ++q) m = std::max(m, std::fabs(tb[q] - N.orig[3 * a + q]));
+        far[a] = std::max(far[a], m + ext[N.e_B[k]] * (T.rot ? std::sqrt(3.0) : 1.0));
+      }
+  });
   double reach = 0;
-  for (int64_t a = 0; a < ng; ++a) {
-    reach = std::max(reach, ext[a]);
-    for (int64_t k = N.e_off[a]; k < N.e_off[a + 1]; ++k) {
-      const int code = N.e_code[k];
-      const Xf T = image_transform(g, code / 9 - 1, (code / 3) % 3 - 1, code % 3 - 1);
-      double tb[3];
-      T.apply(&N.orig[3 * (int64_t)N.e_B[k]], tb);
-      double m = 0;
-      for (int q = 0; q < 3; ++q) m = std::max(m, std::fabs(tb[q] - N.orig[3 * a + q]));
-      reach = std::max(reach, m + ext[N.e_B[k]] * (T.rot ? std::sqrt(3.0) : 1.0));
-    }
-  }
+  for (int64_t a = 0; a < ng; ++a) reach = std::max(reach, far[a]);
   N.reach = reach;
   return AICA_OK;
 }

@@ -77,3 +77,24 @@ def test_cell_scans(A, cells):
         inside = np.ones(n - 1, bool)
         inside[new - 1] = False
         assert (np.diff(order)[inside] > 0).all()        # in ascending order of their ids
+
+
+# lists kept from another molecule count (the cut unchanged) or rebuilt (changed): bit for bit those of a fresh handle
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_molecule_count_changes(A, precision):
+    import torch
+    wl = W.small_random(n_mesh=(6, 5, 4), L=(14.0, 13.0, 12.0), N=1500, seed=29)
+    one = np.ones(1)
+    d = A.DIL(wl.mesh, 2.5)
+    for n in (1500, 1499, 1490, 700, 699, 0, 1, 1500):
+        x = torch.tensor(wl.x[:n], dtype=torch.float64, device="cuda")
+        G = torch.tensor(np.random.default_rng(n).normal(size=(n, 3)), dtype=getattr(torch, "float" + precision[2:]), device="cuda")
+        out = []
+        for h in (d, A.DIL(wl.mesh, 2.5)):
+            A.aica_bin(h, x)
+            F, uw, npairs = A.aica_forces(h, x, None, one, one, precision=precision)
+            gx, ge, gs = A.aica_forces_adjoint(h, x, G, 0.7, None, one, one, precision=precision)
+            out.append([v.cpu().numpy() for v in (F, uw, npairs, gx, ge, gs)] + [h.info()["n_groups"]])
+        print(f"molecule count {n} {precision}: {out[0][-1]} groups", flush=True)
+        for a, b in zip(*out):
+            np.testing.assert_array_equal(a, b)
