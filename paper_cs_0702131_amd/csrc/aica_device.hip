@@ -1614,8 +1614,10 @@ static int prepare_jpart(aica_dil *h, size_t bytes, hipStream_t st) {
 
 // A block of four waves per group up to this many groups, a wave per group beyond: a small system has fewer groups than
 // the chip has SIMDs (1024), so a group's own length is what the call takes.  Pair kernel, FP32, one wave against a
-// block per group: 16 groups 66 and 40 us, 256 groups 80 and 44, 629 groups 70 and 43, 616 groups of two passes 267
-// and 228, 2048 groups 9 us less; 7963 groups 256 and 362 (every wave expands and prunes the whole j-side).
+// block per group: 16 groups 63 and 26 us, 256 groups 77 and 31, 629 groups 69 and 37, 616 groups of two passes 264
+// and 71, 130,000 molecules 121 and 85, 160,000 98 and 104, 7963 groups 257 and 268.  (With every wave listing and
+// pruning the whole j-side the blocks took 40, 44, 43 and 228 us; eight waves gain 4 us on 16 and 256 groups and lose
+// 15 on 629.)
 constexpr int64_t kSplitGroups = 3072;
 
 // The half-list pair kernel: FP32 forces (MODE 0), pair export and per-molecule counts (MODE 1).
@@ -1623,8 +1625,8 @@ template <typename T, int MODE>
 static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool comp, hipStream_t st, int64_t cap,
                        unsigned long long *pcount, int32_t *mol_count = nullptr) {
   using V4 = typename Vec4<T>::type;
-  constexpr int NW = pair_waves(sizeof(T));
   const int64_t ng = h->grp.ng;
+  constexpr int NW = pair_waves(sizeof(T));
   const bool split = MODE == 0 && ng <= kSplitGroups;  // few groups: a whole block per group
   const int64_t nblocks = split ? ng : (ng + NW - 1) / NW;
   const int64_t padded = ((nblocks + 7) / 8) * 8;
