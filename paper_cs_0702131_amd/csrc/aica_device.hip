@@ -354,7 +354,8 @@ __device__ __forceinline__ bool plane_ball(const double *p, const float4 *R, con
 // the face most likely crossed, 32 lanes each (a molecule that a record shows strictly inside a cell is in no other);
 // every other molecule goes to a list.  What bounds the record tests is the latency of their loads: with one lane per
 // molecule (24 planes and up to 24 tetrahedra in turn) this kernel took 39 us on 864 molecules and 0.68 ms on 6.7
-// million, in this form 10 us and 0.54 ms.  k_locate_slow takes the list, a group of lanes per molecule: the FP64
+// million, in this form 10 us and 0.37 ms (0.54 with an atomic per molecule that stays in its
+// a step without moves).  k_locate_slow takes the list, a group of lanes per molecule: the FP64
 // previous-cell test and the cells across the previous cell's faces (a molecule that left its cell has crossed one of
 // them: the paper's membership tracking), each accepted only when the point is strictly inside; then
 // every cell whose padded box holds the point, in ascending mesh cell id (the lowest containing cell wins
@@ -384,8 +385,8 @@ __global__ __launch_bounds__(256) void k_locate_fast(
   const int64_t base = (int64_t)blockIdx.x * MPB;
   if (tid == 0) np = nf = ns = nrec = 0;
   __syncthreads();
-  auto take = [&](int64_t t, int64_t i, int32_t c, const float4 *ball) {
-    if (ball) ref[i] = *ball;
+  auto take = [&](int64_t t, int64_t i, int32_t c, const float4 &ball) {
+    ref[i] = ball;
     cell_t[t] = c;
     rank_t[t] = atomicAdd(&count[c], 1);
   };
@@ -394,22 +395,37 @@ __global__ __launch_bounds__(256) void k_locate_fast(
   for (int k = 0; k < (MPB + 255) / 256; ++k) {
     const int off = k * 256 + tid;
     const int64_t t = base + off;
+    int32_t h0 = -1;
+    bool stay = false;
     if ((MPB >= 256 || off < MPB) && t < n) {
       const int64_t i = trav ? trav[t] : t;
       const double p[3] = {(double)pos[3 * i], (double)pos[3 * i + 1], (double)pos[3 * i + 2]};
-      const int32_t h0 = hint ? hint[t] : -1;
-      bool rec = false, ball = false;
+      if (hint) h0 = hint[t];
+      bool rec = false;
       if (h0 >= 0 && isfinite(p[0]) && isfinite(p[1]) && isfinite(p[2])) {
         // still inside the ball found inside this cell when it was last tested: no record needed
         const float4 b = ref[i];
         const double e0 = p[0] - (double)b.x, e1 = p[1] - (double)b.y, e2 = p[2] - (double)b.z;
-        ball = b.w > 0.f && e0 * e0 + e1 * e1 + e2 * e2 < (double)b.w * (double)b.w;
-        rec = !ball && rec32;
+        stay = b.w > 0.f && e0 * e0 + e1 * e1 + e2 * e2 < (double)b.w * (double)b.w;
+        rec = !stay && rec32;
       }
-      if (ball) take(t, i, h0, nullptr);
+      if (stay) cell_t[t] = h0;
       else if (rec) plane_l[atomicAdd(&np, 1)] = off;
       else slow_l[atomicAdd(&ns, 1)] = off;
     }
+    // the molecules that stay are counted a run of neighbouring lanes with one previous cell at a time
+    const int lane = tid & 63;
+    const int32_t hp = __shfl_up(h0, 1, 64);
+    const unsigned long long upto = ~0ull >> (63 - lane), heads = __builtin_amdgcn_ballot_w64(lane == 0 || hp != h0);
+    const int first = 63 - __builtin_clzll(heads & upto);
+    const unsigned long long after = heads & ~upto;
+    const unsigned long long run = (after ? (1ull << __builtin_ctzll(after)) - 1 : ~0ull) & (~0ull << first) &
+                                   __builtin_amdgcn_ballot_w64(stay);
+    const int lead = run ? (int)__builtin_ctzll(run) : lane;
+    int32_t place = 0;
+    if (stay && lane == lead) place = atomicAdd(&count[h0], (int32_t)__builtin_popcountll(run));
+    place = __shfl(place, lead, 64);
+    if (stay) rank_t[t] = place + (int32_t)__builtin_popcountll(run & (upto >> 1));
   }
   __syncthreads();
   // ---- the plane test of the previous cell, eight lanes per molecule (the group's lanes stay together)
@@ -423,7 +439,7 @@ __global__ __launch_bounds__(256) void k_locate_fast(
     const bool in = plane_ball<8>(p, rec32 + (int64_t)kR32 * h0, pl32 + (int64_t)kPl * h0, ball);
     if ((tid & 7) == 0) {
       if (in) {
-        take(t, i, h0, &ball);
+        take(t, i, h0, ball);
         atomicAdd(&nrec, 1);
       } else {
         fan_l[atomicAdd(&nf, 1)] = off;
@@ -459,7 +475,7 @@ __global__ __launch_bounds__(256) void k_locate_fast(
     }
     if ((tid & 31) == 0) {
       if (found >= 0) {
-        take(t, i, found, &ball);
+        take(t, i, found, ball);
         atomicAdd(&nrec, 1);
       } else {
         slow_l[atomicAdd(&ns, 1)] = off;
