@@ -1371,14 +1371,16 @@ static int make_neigh(aica_dil *h, double density, double target) {
   return AICA_OK;
 }
 
-// Both sets of lists, for n molecules.  They are kept while n leaves the cuts as they are: a program whose molecule
+// Both sets of lists, for n molecules.  Full lists: groups of up to 128 expected molecules, or 64 while that leaves fewer
+// of them than CUs (a pass of FP64 forces and adjoint, us, 64 against 128: 7,000 molecules 168 and 180, 13,000 166 and
+// 188, 28,000 191 and 190, 31,999 of five species 180 and 185; 40,000 232 and 203; with 32 no size is faster).  They are kept while n leaves the cuts as they are: a program whose molecule
 // count changes from step to step rebuilt them at every binning (117 ms of host work at 371,896 molecules, 1.6 s at 6.7
 // million).
 static int ensure_groups(aica_dil *h, int64_t n) {
   const double density = (double)n / h->geo.total_volume;
   double target = 64.0;  // largest expected occupancy of a group (k-d subtree; measured best on the channel)
   if (const char *e = getenv("AICA_GROUP_TARGET")) target = std::max(1.0, atof(e));
-  double nb_target = 128.0;
+  double nb_target = n < 256 * 128 ? 64.0 : 128.0;
   if (const char *e = getenv("AICA_NB_TARGET")) nb_target = std::max(1.0, atof(e));
   const bool keep = h->groups_ready && h->grp.cut.holds(density, target);
   const bool nb_keep = h->neigh_ready && h->nb.cut.holds(density, nb_target);
