@@ -354,8 +354,7 @@ __device__ __forceinline__ bool plane_ball(const double *p, const float4 *R, con
 // the face most likely crossed, 32 lanes each (a molecule that a record shows strictly inside a cell is in no other);
 // every other molecule goes to a list.  What bounds the record tests is the latency of their loads: with one lane per
 // molecule (24 planes and up to 24 tetrahedra in turn) this kernel took 39 us on 864 molecules and 0.68 ms on 6.7
-// million, in this form 10 us and 0.37 ms (0.54 with an atomic per molecule that stays in its
-// a step without moves).  k_locate_slow takes the list, a group of lanes per molecule: the FP64
+// million, in this form 10 us and 0.37 ms (0.54 with an atomic per molecule that stays in its ball).  k_locate_slow takes the list, a group of lanes per molecule: the FP64
 // previous-cell test and the cells across the previous cell's faces (a molecule that left its cell has crossed one of
 // them: the paper's membership tracking), each accepted only when the point is strictly inside; then
 // every cell whose padded box holds the point, in ascending mesh cell id (the lowest containing cell wins
@@ -613,10 +612,10 @@ __device__ OutT block_exclusive_scan(OutT v, OutT *sh, OutT &total) {
 
 // What bounds a small system's binning is its launches (2.5 to 5 us each): both scans are one pass over the cells and,
 // up to kScanDirect cells, one launch.
-// One tile of kScanTile cells; returns the tile's totals and writes the offsets plus c0 / s0.
+// One tile of kScanTile cells: its offsets and totals.
 template <bool HALF>
-__device__ __forceinline__ void scan_tile(const int32_t *count, const int32_t *rcnt, int64_t n, int64_t tile, int32_t c0,
-                                          int64_t s0, int32_t *cell_start, int64_t *slot_base, int32_t &ctot, int64_t &stot) {
+__device__ __forceinline__ void scan_tile(const int32_t *count, const int32_t *rcnt, int64_t n, int64_t tile,
+                                          int32_t *cell_start, int64_t *slot_base, int32_t &ctot, int64_t &stot) {
   __shared__ int32_t shc[kScanThreads / 64 + 1];
   __shared__ int64_t shs[kScanThreads / 64 + 1];
   const int64_t base = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
@@ -629,8 +628,8 @@ __device__ __forceinline__ void scan_tile(const int32_t *count, const int32_t *r
     c += v[k];
     sl += x[k];
   }
-  int32_t ec = block_exclusive_scan<int32_t>(c, shc, ctot) + c0;
-  int64_t es = block_exclusive_scan<int64_t>(sl, shs, stot) + s0;
+  int32_t ec = block_exclusive_scan<int32_t>(c, shc, ctot);
+  int64_t es = block_exclusive_scan<int64_t>(sl, shs, stot);
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
     if (base + k < n) {
@@ -641,22 +640,48 @@ __device__ __forceinline__ void scan_tile(const int32_t *count, const int32_t *r
     es += x[k];
   }
 }
-// A few tiles: one block takes them in turn.
+// Few cells: one block, a run of consecutive cells per thread, read twice (its total, then its offsets).  The loads of a
+// run are all in flight at once: tile after tile, 27,000 cells took 20 us.
 template <bool HALF>
-__global__ __launch_bounds__(kScanThreads) void k_scan_cells(const int32_t *count, const int32_t *rcnt, int64_t n,
-                                                              int32_t *cell_start, int64_t *slot_base,
-                                                              unsigned long long *slots) {
+__global__ __launch_bounds__(kScanThreads) void k_scan_cells(const int32_t *__restrict__ count,
+                                                              const int32_t *__restrict__ rcnt, int64_t n,
+                                                              int32_t *__restrict__ cell_start,
+                                                              int64_t *__restrict__ slot_base,
+                                                              unsigned long long *__restrict__ slots) {
+  __shared__ int32_t shc[kScanThreads / 64 + 1];
+  __shared__ int64_t shs[kScanThreads / 64 + 1];
+  const int64_t per = ((n + kScanThreads - 1) / kScanThreads + 3) & ~(int64_t)3;  // whole int4
+  const int64_t b = min(n, per * threadIdx.x), e = min(n, b + per);
   int32_t c = 0, ct;
   int64_t s = 0, st;
-  for (int64_t t = 0; t * kScanTile < n; ++t) {
-    scan_tile<HALF>(count, rcnt, n, t, c, s, cell_start, slot_base, ct, st);
-    c += ct;
-    s += st;
-  }
+  auto each = [&](auto &&f) {
+    int64_t k = b;
+#pragma unroll 4
+    for (; k + 4 <= e; k += 4) {
+      const int4 v = *reinterpret_cast<const int4 *>(count + k), r = *reinterpret_cast<const int4 *>(rcnt + k);
+      f(k, v.x, r.x);
+      f(k + 1, v.y, r.y);
+      f(k + 2, v.z, r.z);
+      f(k + 3, v.w, r.w);
+    }
+    for (; k < e; ++k) f(k, count[k], rcnt[k]);
+  };
+  each([&](int64_t, int32_t v, int32_t r) {
+    c += v;
+    s += (int64_t)v * r;
+  });
+  c = block_exclusive_scan<int32_t>(c, shc, ct);
+  s = block_exclusive_scan<int64_t>(s, shs, st);
+  each([&](int64_t k, int32_t v, int32_t r) {
+    cell_start[k] = c;
+    if (HALF) slot_base[k] = s;
+    c += v;
+    s += (int64_t)v * r;
+  });
   if (threadIdx.x == 0) {
-    cell_start[n] = c;
-    if (HALF) slot_base[n] = s;
-    *slots = (unsigned long long)s;
+    cell_start[n] = ct;
+    if (HALF) slot_base[n] = st;
+    *slots = (unsigned long long)st;
   }
 }
 // Many tiles: every tile on its own, the tile totals, then the totals before each tile added.
@@ -665,7 +690,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const int32_t *coun
                                                               int32_t *cell_start, int64_t *slot_base, int64_t *tile_sum) {
   int32_t ct;
   int64_t st;
-  scan_tile<HALF>(count, rcnt, n, blockIdx.x, 0, 0, cell_start, slot_base, ct, st);
+  scan_tile<HALF>(count, rcnt, n, blockIdx.x, cell_start, slot_base, ct, st);
   if (threadIdx.x == 0) {
     tile_sum[2 * (int64_t)blockIdx.x] = ct;
     tile_sum[2 * (int64_t)blockIdx.x + 1] = st;
@@ -1004,7 +1029,9 @@ inline int red_blocks(int64_t ng, int64_t &chunk) {
 inline unsigned grid1d(int64_t n, int b) { return (unsigned)std::max<int64_t>(1, (n + b - 1) / b); }
 
 // cell_start, slot_base (half) and the number of reaction slots from the cells' occupancies.
-constexpr int64_t kScanDirect = 8 * kScanTile;  // up to 32,768 cells one block takes about as long as one launch more
+// One block up to 16,384 cells: a binning with 4,225 cells took 48 us with one launch and 55 with three, with 13,824
+// cells 57 either way, with 67,240 143 and 77.
+constexpr int64_t kScanDirect = 4 * kScanTile;
 int scan_cells(aica_dil *h, int64_t nc, bool half, unsigned long long *slots, hipStream_t st) {
   const int64_t ntiles = std::max<int64_t>(1, (nc + kScanTile - 1) / kScanTile);
   const int32_t *count = h->d_count.as<int32_t>(), *rcnt = h->d_rcnt.as<int32_t>();

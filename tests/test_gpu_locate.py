@@ -51,8 +51,10 @@ def test_hints_give_the_searched_cells(A, kind, n, dtype):
             np.testing.assert_array_equal(a, b)
 
 
-# one block's tiles (one, a whole one, one more, the last that it takes), then a launch of tiles
-@pytest.mark.parametrize("cells", [(1, 1, 1), (16, 16, 16), (17, 241, 1), (32, 32, 32), (331, 11, 9)])
+# one block (a cell, four per thread, one more, the last that it takes), then launches of tiles (a cell in the last one,
+# whole ones, a cell more)
+@pytest.mark.parametrize("cells", [(1, 1, 1), (16, 16, 16), (17, 241, 1), (32, 32, 16), (29, 5, 113), (32, 32, 32),
+                                   (331, 11, 9)])
 def test_cell_scans(A, cells):
     import torch
     rng = np.random.default_rng(83)
