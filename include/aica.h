@@ -129,8 +129,9 @@ int aica_build_dil_ex(const aica_mesh *mesh, double rcut, double guard, int32_t 
  * 2^31 reaction records), AICA_E_HIP. */
 int aica_bin(aica_dil *dil, const void *pos_dev, int32_t pos_dtype, int64_t n, void *hip_stream);
 
-/* Per-step forces (Sec. 2.3.1 real-real and 2.3.2 real-referred loops, with
- * the reaction -F applied to the partner, Sec. 2.2): for every unordered pair
+/* Per-step forces (Sec. 2.3.1 real-real and 2.3.2 real-referred loops; the
+ * partner's reaction -F, Sec. 2.2, is either stored or evaluated again from the
+ * partner's side): for every unordered pair
  * {a, T b} (T the image's referring transform x -> R x + y) with
  * |d|^2 < rcut^2, d = x_a - T x_b,
  *   u = 4 eps_ab [(sigma_ab/r)^12 - (sigma_ab/r)^6],  F_a += g d, F_b -= R^T g d,
@@ -158,15 +159,16 @@ int aica_forces(aica_dil *dil, const void *pos_dev, const int32_t *species_dev, 
  * arguments, preconditions and results (bit for bit) as aica_forces, but every
  * buffer of the call lies in a fixed device array of 128 MiB that the library
  * holds on each GPU it runs on until the process ends; the call allocates and
- * frees nothing.  The array holds the cell-sorted positions (16 or 32 bytes per
+ * frees nothing.  A step fits when the cell-sorted positions (16 or 32 bytes per
  * molecule), the own records (32 or 64 bytes per molecule), the reaction records
  * (16 or 32 bytes each, aica_info.n_jslots of them) and per-group partials
- * (32 bytes per group), each region rounded up to 256 bytes, plus 32 KiB; a step
+ * (32 bytes per group), each region rounded up to 256 bytes, plus 32 KiB, fit
+ * (an evaluation without records takes less and is held to the same); a step
  * that needs more fails with AICA_E_INVAL (the message names the bytes needed)
  * and nothing is launched.  The handle and its binning (aica_build_dil, aica_bin)
  * are prepared beforehand by those calls, which may allocate.  The array keeps
- * the last call's contents; each call first clears the reaction records' tags
- * (a fill kernel, no memset).  All calls on one GPU share the array: calls that
+ * the last call's contents; a call that uses reaction records first clears their
+ * tags (a fill kernel, no memset).  All calls on one GPU share the array: calls that
  * overlap in time on one GPU (other streams, other threads, other handles) race
  * and give wrong results; order them on one stream.  aica_profile timing is not
  * recorded for this call.  Errors: AICA_E_INVAL, AICA_E_HIP. */
@@ -184,8 +186,8 @@ int aica_forces_noalloc(aica_dil *dil, const void *pos_dev, const int32_t *speci
  * (1..8 species).  Precision: the pair terms (which carry up
  * to r^-16) are formed in FP64 in both precisions, from the FP32 positions and G
  * with AICA_FP32 (whose differences are exact for multiples of 2^-15), and summed
- * per molecule in FP64; with AICA_FP32 only the roundings of the per-entry
- * partial sums and of the result to FP32 remain.  The parameter gradients are
+ * per molecule in FP64; with AICA_FP32 only the rounding of the result to FP32
+ * remains.  The parameter gradients are
  * the per species-pair sums of dl/deps_ab and dl/dsigma_ab (FP64) taken back to
  * the species through the mixing rule (d eps_ab/d eps_a = eps_ab/(2 eps_a) and
  * d sigma_ab/d sigma_a = 1/2 for a != b).
@@ -203,15 +205,15 @@ int aica_dil_export(const aica_dil *dil, int64_t *n, int32_t *c, int32_t *d, int
 
 /* The molecule pairs the GPU path evaluates inside the cut-off, as (a, b, img)
  * with d = x_a - T_img x_b (a and b in either order; a == b for a molecule and
- * its own image).  Runs the same traversal as
- * aica_forces after aica_bin.  Host output arrays of capacity cap; *n gets the
+ * its own image).  Decides them as aica_forces
+ * does, after aica_bin.  Host output arrays of capacity cap; *n gets the
  * count (which may exceed cap: call again with a larger cap). */
 int aica_pairs_export(aica_dil *dil, const void *pos_dev, const aica_params *params, int64_t cap, int64_t *n,
                       int32_t *a, int32_t *b, int8_t *img, void *hip_stream);
 
 /* Per-molecule pair counts: counts_dev[a] = the number of pairs inside the cut-off that molecule a takes
  * part in (each pair counts for both molecules; a molecule paired with its own image counts twice), from
- * the same traversal as aica_forces after aica_bin.  counts_dev: device int32 [n], caller order,
+ * the binning of aica_bin.  counts_dev: device int32 [n], caller order,
  * overwritten.  params: rcut and precision are used (the cut-off is decided as aica_forces decides it).
  * Same preconditions as aica_forces.  Errors: AICA_E_INVAL, AICA_E_NOMEM, AICA_E_HIP. */
 int aica_pair_counts(aica_dil *dil, const void *pos_dev, const aica_params *params, int32_t *counts_dev,
@@ -243,7 +245,8 @@ int aica_work_stats(const aica_dil *dil, int64_t *dil_candidates, int64_t *lane_
 
 /* Kernel timing with HIP events on the caller's stream: enable, then read the
  * accumulated milliseconds and launch count of a named kernel
- * ("pair_fwd", "pair_adj", "bin", "finalize"), and reset. */
+ * ("pair_fwd", "pair_adj", "bin", "finalize": per-molecule sums of the half
+ * lists, U, W and the pair count), and reset. */
 int aica_profile(aica_dil *dil, int32_t enable);
 int aica_profile_read(aica_dil *dil, const char *kernel, double *ms_total, int64_t *launches, int32_t reset);
 

@@ -1,12 +1,14 @@
 // HIP (gfx950) kernels and the C ABI of the AICA Lennard-Jones library.
 //
 // Per step (aica_bin, then aica_forces / aica_forces_adjoint):
-//   locate -> histogram -> scan -> scatter -> in-cell sort     : CSR cell occupancy (Sec. 2.2)
-//   group ranges, j-slot offsets                               : the per-step work list
+//   locate (and count) -> scan -> scatter -> in-cell sort      : CSR cell occupancy (Sec. 2.2)
 //   gather                                                     : cell-sorted SoA, group-local coordinates
-//   pair kernel                                                : real-real and periodic referred pairs,
-//                                                                Newton reactions (Sec. 2.3.1, 2.3.2, 2.2)
-//   finalize, reduce                                           : per-molecule sums in caller order, U, W
+//   pair kernel                                                : real-real and periodic referred pairs
+//                                                                (Sec. 2.3.1, 2.3.2): the full lists (aica_neigh.inc:
+//                                                                every pair from both sides, forces in caller
+//                                                                order) or the half lists (aica_pair.inc: Newton
+//                                                                reactions, Sec. 2.2, kept as records)
+//   finalize (half lists), reduce                              : per-molecule sums in caller order, U, W
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1986,11 +1988,14 @@ static int forces_noalloc(aica_dil *h, const void *pos_dev, const int32_t *speci
   const size_t b_pos = align256(sizeof(V4) * std::max<int64_t>(n, 1));
   const size_t b_own = align256(sizeof(T) * 8 * std::max<int64_t>(n, 1));
   const size_t b_jpart = align256(sizeof(T) * 4 * std::max<int64_t>(J, 1));
-  const size_t b_gpart = align256(sizeof(double) * 2 * std::max<int64_t>(ng, 1));
-  const size_t b_gnp = align256(16 * std::max<int64_t>(ng, 1));
+  const size_t b_gpart = align256(sizeof(double) * 2 * std::max<int64_t>(h->grp.ng, 1));
+  const size_t b_gnp = align256(16 * std::max<int64_t>(h->grp.ng, 1));
   const size_t b_red = align256(sizeof(double) * 8 * kRedBlocks);
-  const size_t b_box = full ? align256(sizeof(T) * 6 * std::max<int64_t>(ng, 1)) : 0;
-  const size_t need = b_pos + b_box + b_own + b_jpart + b_gpart + b_gnp + b_red;
+  // What the half lists take decides for both whether a step fits, so that it does not depend on which lists run.  The
+  // full lists take less: boxes in place of the records.
+  const size_t b_box = align256(sizeof(T) * 6 * std::max<int64_t>(ng, 1));
+  const size_t b_full = b_pos + b_box + 2 * align256(16 * std::max<int64_t>(ng, 1)) + b_red;
+  const size_t need = std::max(b_pos + b_own + b_jpart + b_gpart + b_gnp + b_red, full ? b_full : 0);
   if (need > kScratchBytes)
     return fail(AICA_E_INVAL, "aica_forces_noalloc needs " + std::to_string(need) + " bytes of scratch for " +
                                   std::to_string(n) + " molecules; the fixed scratch holds " +
@@ -2002,12 +2007,18 @@ static int forces_noalloc(aica_dil *h, const void *pos_dev, const int32_t *speci
   if (rc) return rc;
   ForceWs ws;
   ws.pos = base;
-  ws.box = base + b_pos;
-  ws.own = base + b_pos + b_box;
-  ws.jpart = base + b_pos + b_box + b_own;
-  ws.gpart = base + b_pos + b_box + b_own + b_jpart;
-  ws.gnp = base + b_pos + b_box + b_own + b_jpart + b_gpart;
-  ws.red = base + b_pos + b_box + b_own + b_jpart + b_gpart + b_gnp;
+  if (full) {
+    ws.box = base + b_pos;
+    ws.gpart = base + b_pos + b_box;
+    ws.gnp = (char *)ws.gpart + align256(16 * std::max<int64_t>(ng, 1));
+    ws.red = (char *)ws.gnp + align256(16 * std::max<int64_t>(ng, 1));
+  } else {
+    ws.own = base + b_pos;
+    ws.jpart = base + b_pos + b_own;
+    ws.gpart = base + b_pos + b_own + b_jpart;
+    ws.gnp = base + b_pos + b_own + b_jpart + b_gpart;
+    ws.red = base + b_pos + b_own + b_jpart + b_gpart + b_gnp;
+  }
   if (!full) {
     // the array keeps the last call's records: every record's tag is cleared (a fill kernel, no memset node)
     ws.epoch = 1;
