@@ -96,7 +96,7 @@ def measured_counters(kernel, workload):
 
 
 PAIR_KERNELS = {"pair_fwd": "k_force<float, 0, true, false>", "pair_adj": "k_force_adj<float, 0, false>"}
-TIMERS = ("pair_fwd", "pair_adj", "bin", "finalize", "finalize_adj")
+TIMERS = ("pair_fwd", "pair_adj", "bin", "finalize")
 
 
 def moving_sets(wl, count, step=0.005, seed=11):
