@@ -1478,11 +1478,11 @@ void aica_dil_free(aica_dil *h) {
 }
 
 // Which lists a force call runs on.  The full lists (k_force: every pair from both sides, no reaction records) take
-// FP64, and FP32 from 200,000 molecules on: the channel's 6.7M molecules take 1.65 ms in place of 2.50 ms (pair
-// kernel) and 0.34 ms (finalize), a step (bin, forces, adjoint) of the 219,488-molecule mixture 0.50 ms in place of
-// 0.60.  Below that, and with rotating referral, FP32 keeps the half lists: U and W are sums of FP32 terms whose
-// partial sums round to about 1e-9 of the result at 1e4 to 1e5 molecules (at 4e5 across a rotation, where U and W
-// cancel more), and with the half lists they keep the tile-wise partial sums they had.
+// FP64, and FP32 from 200,000 molecules on: 6.7 million molecules take 1.50 ms in place of 2.50 ms (pair kernel) and
+// 0.34 ms (finalize); a step (bin, forces, adjoint) of a mixture of 219,488 took 0.50 ms in place of 0.60 when forces and
+// adjoint had moved and nothing else.  Below that, and with rotating referral, FP32 keeps the half lists: U and W are
+// sums of FP32 terms whose partial sums round to about 1e-9 of the result at 1e4 to 1e5 molecules (at 4e5 across a
+// rotation, where U and W cancel more), and with the half lists they keep the tile-wise partial sums they had.
 static bool full_lists(const aica_dil *h, int64_t n, int tsize) { return tsize == 8 || (n >= 200000 && !h->geo.has_rot); }
 
 int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, void *hip_stream) {
