@@ -111,7 +111,11 @@ struct aica_dil {
   DBuf d_orig, d_g_cell0, d_e_off, d_e_B, d_e_vec32, d_e_vec64, d_nl_off, d_nl_e, d_nl_d, d_nl_r, d_rcnt;
   // full neighbour lists of the force kernel (its own groups; same lifetime)
   Neigh nb;
-  DBuf d_nb_cell0, d_nb_run_off, d_nb_runs, d_nb_eB, d_nb_erev, d_nb_vec32, d_nb_vec64, d_nb_orig, d_nb_eoff;
+  DBuf d_nb_cell0, d_nb_run_off, d_nb_runs, d_nb_vec32, d_nb_vec64, d_nb_orig, d_nb_eoff;
+  DBuf d_of_cell, d_half;       // the half lists' group of each sorted cell; HalfFrames
+  // a pair vector formed in the frames of the full lists differs per axis from that of the half lists by at most
+  // (half an ulp of the compute type) * frame_reach + frame_err
+  double frame_reach = 0, frame_err = 0;
   DBuf d_box;                   // [groups][6] box of each group's molecules in its frame (compute type)
   // rotating referral: the groups of the full lists without a turned entry, then those with one
   DBuf d_nb_glist;
@@ -846,12 +850,18 @@ struct LJTab {
   float rc2, band;
   float rc2lo, rc2hi;  // rc^2 -+ band: an FP32 s below rc2lo is surely inside, at or above rc2hi surely outside
   double rc2d;
-  // rc^2 -+ the most that the two sides of a pair can differ by in its square (rounding of positions referred
-  // between group frames, and of the square): in between, both sides take the canonical side's decision
+  // rc^2 -+ the most that a full list's square of a pair can differ by from the half lists' (rounding of positions in, and
+  // of offsets between, the group frames of either, and of the square): in between, the half lists' decision is taken
   float near_lo, near_hi;
   double near_lod, near_hid;
+  // radius^2 within which the full lists' box test and search keep every pair: rc^2, or near_hi less what those allow anyway
+  double reach2, reach2d;
   int nsp;
 };
+template <typename T>
+__device__ __forceinline__ double reach2(const LJTab &t) {
+  if constexpr (sizeof(T) == 4) return t.reach2; else return t.reach2d;
+}
 template <typename T>
 __device__ __forceinline__ T near_lo(const LJTab &t) {
   if constexpr (sizeof(T) == 4) return t.near_lo; else return t.near_lod;
@@ -1332,6 +1342,10 @@ static int make_groups(aica_dil *h, double density, double target) {
     if ((rc = upload(h->d_rcnt, rcnt))) return rc;
   }
   if ((rc = upload(h->d_orig, G.orig))) return rc;
+  if ((rc = upload(h->d_of_cell, G.of_cell))) return rc;
+  const HalfFrames hf{h->d_of_cell.as<int32_t>(), h->d_orig.as<double>(), h->d_e_off.as<int64_t>(), h->d_e_B.as<int32_t>(),
+                      h->d_e_vec32.as<float4>(), h->d_e_vec64.as<double4>()};
+  if ((rc = upload(h->d_half, std::vector<HalfFrames>{hf}))) return rc;
   h->groups_ready = true;
   return AICA_OK;
 }
@@ -1377,9 +1391,7 @@ static int make_neigh(aica_dil *h, double density, double target) {
   if ((rc = upload(h->d_nb_cell0, N.cell0))) return rc;
   if ((rc = upload(h->d_nb_run_off, N.run_off))) return rc;
   if ((rc = upload(h->d_nb_runs, N.runs))) return rc;
-  if ((rc = upload(h->d_nb_eB, N.e_B))) return rc;
   if ((rc = upload(h->d_nb_eoff, N.e_off))) return rc;
-  if ((rc = upload(h->d_nb_erev, N.e_rev))) return rc;
   if ((rc = upload(h->d_nb_vec32, v32))) return rc;
   if ((rc = upload(h->d_nb_vec64, v64))) return rc;
   if ((rc = upload(h->d_nb_orig, N.orig))) return rc;
@@ -1418,6 +1430,12 @@ static int ensure_groups(aica_dil *h, int64_t n) {
   int rc;
   if (!keep && (rc = make_groups(h, density, target))) return rc;
   if (!nb_keep && (rc = make_neigh(h, density, nb_target))) return rc;
+  // Half-ulp roundings per axis of a pair vector: a translated one's at most three of the frame's reach (the two
+  // positions in their groups' frames, the offset, the sum), a rotated one's six; and in FP64, at the size of the
+  // coordinates themselves, those of the offsets (T orig_B - orig_A), and how far a transform and its inverse miss.
+  const bool rot = h->geo.has_rot;
+  h->frame_reach = (rot ? 6.0 : 3.0) * (h->nb.reach + h->grp.reach);
+  h->frame_err = std::ldexp(1.0, -53) * (rot ? 20.0 : 2.5) * coordinate_size(h->geo) + transform_skew(h->geo);
   h->group_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   return AICA_OK;
 }
@@ -1620,12 +1638,18 @@ static int build_tab(const aica_dil *h, const aica_params *p, LJTab &t) {
   t.band = (float)(t.rc2d * std::ldexp(1.0, -20));
   t.rc2lo = (float)(t.rc2d - (double)t.band);
   t.rc2hi = (float)(t.rc2d + (double)t.band);
-  // per axis a referred position is rounded by at most half an ulp of reach on either side of the pair
-  auto near = [&](double half_ulp) { return 8.0 * p->rcut * h->nb.reach * half_ulp + 16.0 * t.rc2d * half_ulp; };
-  t.near_lo = (float)(t.rc2d - near(std::ldexp(1.0, -24)));
-  t.near_hi = (float)(t.rc2d + near(std::ldexp(1.0, -24)));
-  t.near_lod = t.rc2d - near(std::ldexp(1.0, -53));
-  t.near_hid = t.rc2d + near(std::ldexp(1.0, -53));
+  // the square of a pair at about rc whose vector is off by at most err per axis, and the roundings of the square
+  auto near = [&](double half_ulp) {
+    const double err = half_ulp * h->frame_reach + h->frame_err;
+    return 3.5 * p->rcut * err + 3.0 * err * err + 16.0 * t.rc2d * half_ulp;
+  };
+  const double n32 = near(std::ldexp(1.0, -24)), n64 = near(std::ldexp(1.0, -53));
+  t.near_lo = (float)(t.rc2d - n32);
+  t.near_hi = (float)(t.rc2d + n32);
+  t.near_lod = t.rc2d - n64;
+  t.near_hid = t.rc2d + n64;
+  t.reach2 = std::max(t.rc2d, (t.rc2d + n32) * (1.0 - 5e-5));
+  t.reach2d = std::max(t.rc2d, (t.rc2d + n64) * (1.0 - 5e-5));
   t.nsp = p->n_species;
   return AICA_OK;
 }
@@ -1735,13 +1759,15 @@ static NbLists nb_lists(const aica_dil *h, int part) {
   nl.run_off = h->d_nb_run_off.as<int64_t>();
   nl.runs = h->d_nb_runs.as<int4>();
   nl.e_off = h->d_nb_eoff.as<int64_t>();
-  nl.e_B = h->d_nb_eB.as<int32_t>();
-  nl.e_rev = h->d_nb_erev.as<int32_t>();
   nl.e_vec = sizeof(T) == 4 ? h->d_nb_vec32.p : h->d_nb_vec64.p;
   nl.e_vec64 = h->d_nb_vec64.as<double4>();
   nl.rot = h->geo.has_rot ? h->d_rot64.as<double>() : nullptr;
   nl.list = nullptr;
   nl.ng = h->nb.ng;
+  nl.half = h->d_half.as<HalfFrames>();
+  nl.caller_pos = h->bin_pos;
+  nl.cell_of = h->d_cell_sorted.as<int32_t>();
+  nl.pos64 = h->bin_dtype == AICA_FP64;
   if (h->geo.has_rot) {
     nl.list = h->d_nb_glist.as<int32_t>() + (part ? h->nb_plain_groups : 0);
     nl.ng = part ? h->nb.ng - h->nb_plain_groups : h->nb_plain_groups;

@@ -99,6 +99,11 @@ void spatial_order(const Geometry &g, std::vector<int32_t> &order, std::vector<i
 // Image n of the periodic directions: T_1^n0 T_2^n1 T_3^n2 (the transforms commute).
 Xf image_transform(const Geometry &g, int n0, int n1, int n2);
 
+// Largest coordinate (any axis) of a mesh point or of a first image's shift, summed.
+double coordinate_size(const Geometry &g);
+// How far any first image of the mesh's points, taken back by the opposite image, can miss them (any axis).
+double transform_skew(const Geometry &g);
+
 // One interacting cell pair in sorted cell indices: sc < sd, or sc == sd with img > 0 (lexicographic).
 struct CellPair {
   int32_t sc, sd;
@@ -138,6 +143,7 @@ struct Groups {
   std::vector<int32_t> nl_d;    // sorted cell id (in group B)
   std::vector<int32_t> nl_r;    // 1 + rank of the entry in the cell's reverse list (0 is the self entry)
   std::vector<int64_t> rc_off;  // [nc+1] offsets of the entries whose needed list holds cell d
+  double reach = 0;             // as Neigh::reach
 };
 
 int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
@@ -159,7 +165,6 @@ struct Neigh {
   std::vector<int64_t> e_off;    // [ng+1] entries (j-group, image) of each group, without the group itself
   std::vector<int32_t> e_B;      // j-group
   std::vector<int8_t> e_code;    // image code 9 (n0 + 1) + 3 (n1 + 1) + (n2 + 1)
-  std::vector<int32_t> e_rev;    // the entry of j-group B that refers back (group A, image -n)
   std::vector<int64_t> run_off;  // [ng+1]
   std::vector<CellRun> runs;
   double reach = 0;              // largest coordinate (any axis) of a listed molecule in a group's frame

@@ -82,6 +82,32 @@ Xf image_transform(const Geometry &g, int n0, int n1, int n2) {
   return t;
 }
 
+double coordinate_size(const Geometry &g) {
+  double x = 0, y = 0;
+  for (int q = 0; q < 3; ++q) x = std::max({x, std::fabs(g.dom_lo[q]), std::fabs(g.dom_hi[q])});
+  for (int c = 0; c < 27; ++c) {
+    const Xf t = image_transform(g, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
+    for (int q = 0; q < 3; ++q) y = std::max(y, std::fabs(t.y[q]));
+  }
+  return x + y;
+}
+
+double transform_skew(const Geometry &g) {
+  if (!g.has_rot) return 0;  // lattice translations are taken back exactly
+  const double size = coordinate_size(g);
+  double m = 0;
+  for (int c = 0; c < 27; ++c) {
+    const Xf t = image_transform(g, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
+    const Xf b = t.then(image_transform(g, 1 - c / 9, 1 - (c / 3) % 3, 1 - c % 3));
+    for (int i = 0; i < 3; ++i) {
+      double v = std::fabs(b.y[i]);
+      for (int j = 0; j < 3; ++j) v += std::fabs(b.R[3 * i + j] - (i == j ? 1.0 : 0.0)) * size;
+      m = std::max(m, v);
+    }
+  }
+  return m;
+}
+
 static bool same_xf(const Xf &a, const Xf &b, double scale) {
   for (int i = 0; i < 9; ++i)
     if (std::fabs(a.R[i] - b.R[i]) > 1e-12) return false;
@@ -847,6 +873,38 @@ static void cut_groups(const Geometry &g, const std::vector<int32_t> &order, con
   cut.whole_vol = whole_vol;
 }
 
+// Largest coordinate (any axis) of a molecule of a group, or of one that its entries refer to it, in its frame.
+template <class F>
+static double group_reach(const Geometry &g, const std::vector<int32_t> &order, const std::vector<int32_t> &cell0,
+                          const std::vector<double> &orig, const std::vector<int64_t> &e_off,
+                          const std::vector<int32_t> &e_B, F code_of) {
+  const int64_t ng = (int64_t)cell0.size() - 1;
+  Xf T[27];
+  for (int c = 0; c < 27; ++c) T[c] = image_transform(g, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
+  std::vector<double> ext(ng, 0.0);  // the group's box about its origin
+  parallel_for(ng, [&](int64_t b, int64_t e, int) {
+    for (int64_t a = b; a < e; ++a)
+      for (int32_t sc = cell0[a]; sc < cell0[a + 1]; ++sc)
+        for (int q = 0; q < 3; ++q) {
+          const int64_t c = order[sc];
+          ext[a] = std::max({ext[a], std::fabs(g.lo[3 * c + q] - orig[3 * a + q]), std::fabs(g.hi[3 * c + q] - orig[3 * a + q])});
+        }
+  });
+  std::vector<double> far(ext);
+  parallel_for(ng, [&](int64_t b, int64_t e, int) {
+    for (int64_t a = b; a < e; ++a)
+      for (int64_t k = e_off[a]; k < e_off[a + 1]; ++k) {
+        const Xf &t = T[code_of(k)];
+        double tb[3];
+        t.apply(&orig[3 * (int64_t)e_B[k]], tb);
+        double m = 0;
+        for (int q = 0; q < 3; ++q) m = std::max(m, std::fabs(tb[q] - orig[3 * a + q]));
+        far[a] = std::max(far[a], m + ext[e_B[k]] * (t.rot ? std::sqrt(3.0) : 1.0));
+      }
+  });
+  return *std::max_element(far.begin(), far.end());
+}
+
 int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
                  const std::vector<CellPair> &pairs, double density, double target, Groups &G) {
   const int64_t nc = g.nc;
@@ -974,6 +1032,9 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
     const int32_t d = G.nl_d[k];
     G.nl_r[k] = (int32_t)(1 + cfill[d]++ - G.rc_off[d]);
   }
+  G.reach = group_reach(g, order, G.cell0, G.orig, G.e_off, G.e_B, [&](int64_t k) {
+    return img_code(G.e_img[3 * k], G.e_img[3 * k + 1], G.e_img[3 * k + 2]);
+  });
   return AICA_OK;
 }
 
@@ -990,9 +1051,8 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
   std::vector<int32_t> of_cell(nc);
   for (int64_t a = 0; a < ng; ++a)
     for (int64_t s = N.cell0[a]; s < N.cell0[a + 1]; ++s) of_cell[s] = (int32_t)a;
-  // origins: mean of member centroids rounded to a multiple of 2^-15; reach: the group's box about its origin
+  // origins: mean of member centroids rounded to a multiple of 2^-15
   N.orig.assign(3 * ng, 0.0);
-  std::vector<double> ext(ng);
   parallel_for(ng, [&](int64_t b, int64_t e, int) {
     for (int64_t a = b; a < e; ++a) {
       double s[3] = {0, 0, 0};
@@ -1000,12 +1060,6 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
         for (int q = 0; q < 3; ++q) s[q] += g.ccen[3 * (int64_t)order[sc] + q];
       const double n = N.cell0[a + 1] - N.cell0[a];
       for (int q = 0; q < 3; ++q) N.orig[3 * a + q] = std::ldexp(std::nearbyint(std::ldexp(s[q] / n, 15)), -15);
-      ext[a] = 0;
-      for (int32_t sc = N.cell0[a]; sc < N.cell0[a + 1]; ++sc)
-        for (int q = 0; q < 3; ++q) {
-          const int64_t c = order[sc];
-          ext[a] = std::max({ext[a], std::fabs(g.lo[3 * c + q] - N.orig[3 * a + q]), std::fabs(g.hi[3 * c + q] - N.orig[3 * a + q])});
-        }
     }
   });
   std::vector<int64_t> pstart(ng + 1, 0);
@@ -1107,7 +1161,6 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
   if (E >= (1LL << 31)) return fail(AICA_E_NOMEM, "too many group pairs");
   N.e_B.resize(E);
   N.e_code.resize(E);
-  N.e_rev.resize(E);
   N.runs.resize(N.run_off[ng]);
   parallel_for(ng, [&](int64_t b, int64_t e, int) {
     for (int64_t a = b; a < e; ++a) {
@@ -1117,8 +1170,6 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
         const int code = (int)(ek >> 32);
         N.e_B[k] = B;
         N.e_code[k] = (int8_t)code;
-        const int64_t back = ((int64_t)(26 - code) << 32) | a;
-        N.e_rev[k] = (int32_t)(N.e_off[B] + (std::lower_bound(ents[B].begin(), ents[B].end(), back) - ents[B].begin()));
         ++k;
       }
       CellRun *o = N.runs.data() + N.run_off[a];
@@ -1128,22 +1179,7 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
       }
     }
   });
-  std::vector<double> far(ext);
-  parallel_for(ng, [&](int64_t b, int64_t e, int) {
-    for (int64_t a = b; a < e; ++a)
-      for (int64_t k = N.e_off[a]; k < N.e_off[a + 1]; ++k) {
-        const int code = N.e_code[k];
-        const Xf T = image_transform(g, code / 9 - 1, (code / 3) % 3 - 1, code % 3 - 1);
-        double tb[3];
-        T.apply(&N.orig[3 * (int64_t)N.e_B[k]], tb);
-        double m = 0;
-        for (int q = 0; q < 3; ++q) m = std::max(m, std::fabs(tb[q] - N.orig[3 * a + q]));
-        far[a] = std::max(far[a], m + ext[N.e_B[k]] * (T.rot ? std::sqrt(3.0) : 1.0));
-      }
-  });
-  double reach = 0;
-  for (int64_t a = 0; a < ng; ++a) reach = std::max(reach, far[a]);
-  N.reach = reach;
+  N.reach = group_reach(g, order, N.cell0, N.orig, N.e_off, N.e_B, [&](int64_t k) { return (int)N.e_code[k]; });
   return AICA_OK;
 }
 
