@@ -111,7 +111,7 @@ struct aica_dil {
   DBuf d_orig, d_g_cell0, d_e_off, d_e_B, d_e_vec32, d_e_vec64, d_nl_off, d_nl_e, d_nl_d, d_nl_r, d_rcnt;
   // full neighbour lists of the force kernel (its own groups; same lifetime)
   Neigh nb;
-  DBuf d_nb_cell0, d_nb_run_off, d_nb_runs, d_nb_vec32, d_nb_vec64, d_nb_orig, d_nb_eoff;
+  DBuf d_nb_cell0, d_nb_run_off, d_nb_runs, d_nb_vec32, d_nb_vec64, d_nb_orig, d_nb_eoff, d_nb_ioff, d_nb_imask;
   DBuf d_of_cell, d_half;       // the half lists' group of each sorted cell; HalfFrames
   // a pair vector formed in the frames of the full lists differs per axis from that of the half lists by at most
   // (half an ulp of the compute type) * frame_reach + frame_err
@@ -1350,10 +1350,12 @@ static int make_groups(aica_dil *h, double density, double target) {
   return AICA_OK;
 }
 
-// The full lists' groups and lists.
+// The full lists' groups and lists (with the vertex predicate, those with masks).
 static int make_neigh(aica_dil *h, double density, double target) {
   h->neigh_ready = false;
-  int rc = build_neigh(h->geo, h->order, h->split_depth, h->pairs, h->predicate == AICA_DIL_VERTEX, density, target, h->nb);
+  int rc = h->predicate == AICA_DIL_VERTEX
+               ? build_neigh_masked(h->geo, h->order, h->split_depth, h->grp, density, target, h->nb)
+               : build_neigh(h->geo, h->order, h->split_depth, h->pairs, density, target, h->nb);
   if (rc) return rc;
   const Neigh &N = h->nb;
   const int64_t NE = N.e_off[N.ng];
@@ -1392,6 +1394,8 @@ static int make_neigh(aica_dil *h, double density, double target) {
   if ((rc = upload(h->d_nb_run_off, N.run_off))) return rc;
   if ((rc = upload(h->d_nb_runs, N.runs))) return rc;
   if ((rc = upload(h->d_nb_eoff, N.e_off))) return rc;
+  if ((rc = upload(h->d_nb_ioff, N.i_off))) return rc;
+  if ((rc = upload(h->d_nb_imask, N.i_mask))) return rc;
   if ((rc = upload(h->d_nb_vec32, v32))) return rc;
   if ((rc = upload(h->d_nb_vec64, v64))) return rc;
   if ((rc = upload(h->d_nb_orig, N.orig))) return rc;
@@ -1424,7 +1428,9 @@ static int ensure_groups(aica_dil *h, int64_t n) {
   double nb_target = n < 256 * 128 ? 64.0 : 128.0;
   if (const char *e = getenv("AICA_NB_TARGET")) nb_target = std::max(1.0, atof(e));
   const bool keep = h->groups_ready && h->grp.cut.holds(density, target);
-  const bool nb_keep = h->neigh_ready && h->nb.cut.holds(density, nb_target);
+  // the lists with masks depend on the half lists as well
+  const bool nb_keep =
+      h->neigh_ready && h->nb.cut.holds(density, nb_target) && (keep || h->predicate != AICA_DIL_VERTEX);
   if (keep && nb_keep) return AICA_OK;
   auto t0 = std::chrono::steady_clock::now();
   int rc;
@@ -1501,7 +1507,11 @@ void aica_dil_free(aica_dil *h) {
 // adjoint had moved and nothing else.  Below that, and with rotating referral, FP32 keeps the half lists: U and W are
 // sums of FP32 terms whose partial sums round to about 1e-9 of the result at 1e4 to 1e5 molecules (at 4e5 across a
 // rotation, where U and W cancel more), and with the half lists they keep the tile-wise partial sums they had.
-static bool full_lists(const aica_dil *h, int64_t n, int tsize) { return tsize == 8 || (n >= 200000 && !h->geo.has_rot); }
+// With the vertex predicate both precisions keep them: it does not list every pair in range, and the half lists decide
+// which are left out.
+static bool full_lists(const aica_dil *h, int64_t n, int tsize) {
+  return h->predicate != AICA_DIL_VERTEX && (tsize == 8 || (n >= 200000 && !h->geo.has_rot));
+}
 
 int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, void *hip_stream) {
   if (!h) return fail(AICA_E_INVAL, "handle is NULL");
@@ -1691,14 +1701,15 @@ static int prepare_jpart(aica_dil *h, size_t bytes, hipStream_t st) {
 // 15 on 629.)
 constexpr int64_t kSplitGroups = 3072;
 
-// The half-list pair kernel: FP32 forces (MODE 0), pair export and per-molecule counts (MODE 1).
+// The half-list pair kernel: forces (MODE 0), pair export and per-molecule counts (MODE 1).
 template <typename T, int MODE>
 static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool comp, hipStream_t st, int64_t cap,
                        unsigned long long *pcount, int32_t *mol_count = nullptr) {
   using V4 = typename Vec4<T>::type;
   const int64_t ng = h->grp.ng;
   constexpr int NW = pair_waves(sizeof(T));
-  const bool split = MODE == 0 && ng <= kSplitGroups;  // few groups: a whole block per group
+  constexpr bool SPLITS = MODE == 0 && sizeof(T) == 4;
+  const bool split = SPLITS && ng <= kSplitGroups;  // few groups: a whole block per group
   const int64_t nblocks = split ? ng : (ng + NW - 1) / NW;
   const int64_t padded = ((nblocks + 7) / 8) * 8;
   const V4 *pos = (const V4 *)ws.pos;
@@ -1720,7 +1731,7 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
                      rot, evd, h->d_perm.as<int32_t>(), cap, pairs_out, pcount, mol_count, ws.epoch)
 #define AICA_LAUNCH_R(MIX, COMP, ROT)                    \
   do {                                                   \
-    if constexpr (MODE == 0) {                           \
+    if constexpr (SPLITS) {                              \
       if (split) AICA_LAUNCH_S(MIX, COMP, ROT, true);    \
       else AICA_LAUNCH_S(MIX, COMP, ROT, false);         \
     } else {                                             \
@@ -1732,7 +1743,7 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
     if (nsp == 1) AICA_LAUNCH_R(0, true, true);
     else if (nsp == 2) AICA_LAUNCH_R(1, true, true);
     else AICA_LAUNCH_R(2, true, true);
-  } else if (MODE == 1 || comp) {
+  } else if (MODE == 1 || (comp && sizeof(T) == 4)) {  // compensated sums exist in FP32 only
     if (nsp == 1) AICA_LAUNCH(0, true);
     else if (nsp == 2) AICA_LAUNCH(1, true);
     else AICA_LAUNCH(2, true);
@@ -1748,7 +1759,7 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
   return AICA_OK;
 }
 
-// The full lists, over all groups or (rotating referral) over the groups without (part 0) or with a turned entry (1):
+// The full lists, over all groups (part -1) or, with rotating referral, over those without (0) or with a turned entry (1):
 // the kernels with rotations hold fewer blocks per CU and form the pair vector in more steps, and only the groups along
 // the coupled sides need them (371,896-molecule wedge, FP32 adjoint: 284 us for all groups with rotations, 151 + 89 in
 // two launches).
@@ -1768,7 +1779,9 @@ static NbLists nb_lists(const aica_dil *h, int part) {
   nl.caller_pos = h->bin_pos;
   nl.cell_of = h->d_cell_sorted.as<int32_t>();
   nl.pos64 = h->bin_dtype == AICA_FP64;
-  if (h->geo.has_rot) {
+  nl.i_off = h->d_nb_ioff.as<int64_t>();
+  nl.i_mask = h->d_nb_imask.as<uint32_t>();
+  if (h->geo.has_rot && part >= 0) {
     nl.list = h->d_nb_glist.as<int32_t>() + (part ? h->nb_plain_groups : 0);
     nl.ng = part ? h->nb.ng - h->nb_plain_groups : h->nb_plain_groups;
   }
@@ -1814,22 +1827,31 @@ static int launch_force(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool c
 template <typename T>
 static int launch_adj(aica_dil *h, const LJTab &tab, const AdjTab &at, void *out, hipStream_t st) {
   using V4 = typename Vec4<T>::type;
-#define AICA_LAUNCH_ADJ(MIX, ROT)                                                                                    \
-  hipLaunchKernelGGL((k_force_adj<T, MIX, ROT>), dim3((unsigned)padded), dim3(kNbThreads), 0, st, nl,                \
+#define AICA_LAUNCH_ADJ(MIX, ROT, MASK)                                                                              \
+  hipLaunchKernelGGL((k_force_adj<T, MIX, ROT, MASK>), dim3((unsigned)padded), dim3(kNbThreads), 0, st, nl,          \
                      h->d_pos.as<V4>(), h->d_gG.as<V4>(), h->d_box.as<T>(), h->d_cell_start.as<int32_t>(),           \
                      h->d_perm.as<int32_t>(), padded, tab, at, (T *)out, h->d_gpar.as<double>())
-  for (int part = 0; part < (h->geo.has_rot ? 2 : 1); ++part) {
+  const bool vertex = h->predicate == AICA_DIL_VERTEX;  // lists with masks, in one launch
+  for (int part = vertex ? -1 : 0; part < (vertex ? 0 : h->geo.has_rot ? 2 : 1); ++part) {
     const NbLists nl = nb_lists<T>(h, part);
     const int64_t padded = ((nl.ng + 7) / 8) * 8;
     if (nl.ng == 0) continue;
-    if (part == 1) {
-      if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, true);
-      else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, true);
-      else AICA_LAUNCH_ADJ(2, true);
+    if (part < 0 && h->geo.has_rot) {
+      if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, true, true);
+      else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, true, true);
+      else AICA_LAUNCH_ADJ(2, true, true);
+    } else if (part < 0) {
+      if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, false, true);
+      else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, false, true);
+      else AICA_LAUNCH_ADJ(2, false, true);
+    } else if (part == 1) {
+      if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, true, false);
+      else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, true, false);
+      else AICA_LAUNCH_ADJ(2, true, false);
     } else {
-      if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, false);
-      else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, false);
-      else AICA_LAUNCH_ADJ(2, false);
+      if (tab.nsp == 1) AICA_LAUNCH_ADJ(0, false, false);
+      else if (tab.nsp == 2) AICA_LAUNCH_ADJ(1, false, false);
+      else AICA_LAUNCH_ADJ(2, false, false);
     }
   }
 #undef AICA_LAUNCH_ADJ
@@ -1929,20 +1951,18 @@ static int forces_impl(aica_dil *h, const ForceWs &ws, const void *pos_dev, cons
     ProfScope ps(h, "pair_fwd", st);
     if (full) {
       if ((rc = launch_force<T>(h, ws, tab, comp, forces_dev, st))) return rc;
-    } else if constexpr (sizeof(T) == 4) {
+    } else {
       if ((rc = launch_pair<T, 0>(h, ws, tab, comp, st, 0, nullptr))) return rc;
     }
     h->wsteps_groups = ws.gnp == h->d_gnp.p ? ng : 0;  // the lane-pair diagnostic reads the handle's partials
   }
   {
     ProfScope ps(h, "finalize", st);
-    if constexpr (sizeof(T) == 4) {
-      if (!full && n > 0 && forces_dev) {
-        if (comp)
-          launch_finalize<T, true>(h, ws, forces_dev, st);
-        else
-          launch_finalize<T, false>(h, ws, forces_dev, st);
-      }
+    if (!full && n > 0 && forces_dev) {
+      if (comp && sizeof(T) == 4)
+        launch_finalize<T, true>(h, ws, forces_dev, st);
+      else
+        launch_finalize<T, false>(h, ws, forces_dev, st);
     }
     if (uw_dev || npairs_dev) {
       int64_t chunk;

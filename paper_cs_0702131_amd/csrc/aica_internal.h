@@ -156,7 +156,7 @@ struct CellRun {
 
 // Full neighbour lists of the interaction groups: every group lists all the cells its molecules can have a
 // partner in (both directions of every interacting cell pair), so that each molecule's sum is complete in
-// its own group.
+// its own group.  They hold the molecule pairs of the half lists.
 struct Neigh {
   int64_t ng = 0;
   GroupCut cut;
@@ -168,9 +168,20 @@ struct Neigh {
   std::vector<int64_t> run_off;  // [ng+1]
   std::vector<CellRun> runs;
   double reach = 0;              // largest coordinate (any axis) of a listed molecule in a group's frame
+  // Lists with masks (build_neigh_masked) only: the entries whose molecules a cell's molecules pair with, a row of
+  // (entries of its group + 31) / 32 words for each cell, bit k of a row the group's k-th entry.  The group's own cells
+  // are read through entries too (image 0 of the group itself, first in its runs).
+  std::vector<int64_t> i_off;    // [ng] the group's first word in i_mask
+  std::vector<uint32_t> i_mask;
 };
 
 int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
-                const std::vector<CellPair> &pairs, bool whole_groups, double density, double target, Neigh &out);
+                const std::vector<CellPair> &pairs, double density, double target, Neigh &out);
+
+// Full lists for cell pairs that do not hold every pair in range (the vertex predicate).  The molecule pairs of the half
+// lists are then a matter of both cells: those of group A's cells with the cells of B that A needs, and all of a group's
+// own.  An entry takes the cells of a j-group that pair with the same cells of the group.
+int build_neigh_masked(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
+                       const Groups &G, double density, double target, Neigh &out);
 
 }  // namespace aica

@@ -7,9 +7,11 @@
 #include <cstdlib>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <numeric>
 #include <thread>
+#include <utility>
 
 #include "aica_internal.h"
 
@@ -873,6 +875,22 @@ static void cut_groups(const Geometry &g, const std::vector<int32_t> &order, con
   cut.whole_vol = whole_vol;
 }
 
+// Origins: mean of member centroids rounded to a multiple of 2^-15.
+static void group_origins(const Geometry &g, const std::vector<int32_t> &order, const std::vector<int32_t> &cell0,
+                          std::vector<double> &orig) {
+  const int64_t ng = (int64_t)cell0.size() - 1;
+  orig.assign(3 * ng, 0.0);
+  parallel_for(ng, [&](int64_t b, int64_t e, int) {
+    for (int64_t a = b; a < e; ++a) {
+      double s[3] = {0, 0, 0};
+      for (int32_t sc = cell0[a]; sc < cell0[a + 1]; ++sc)
+        for (int q = 0; q < 3; ++q) s[q] += g.ccen[3 * (int64_t)order[sc] + q];
+      const double n = cell0[a + 1] - cell0[a];
+      for (int q = 0; q < 3; ++q) orig[3 * a + q] = std::ldexp(std::nearbyint(std::ldexp(s[q] / n, 15)), -15);
+    }
+  });
+}
+
 // Largest coordinate (any axis) of a molecule of a group, or of one that its entries refer to it, in its frame.
 template <class F>
 static double group_reach(const Geometry &g, const std::vector<int32_t> &order, const std::vector<int32_t> &cell0,
@@ -917,15 +935,7 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
   G.cell0.push_back((int32_t)nc);
   G.ng = (int64_t)G.cell0.size() - 1;
   const int64_t ng = G.ng;
-  // origins: mean of member centroids rounded to a multiple of 2^-15
-  G.orig.assign(3 * ng, 0.0);
-  for (int64_t a = 0; a < ng; ++a) {
-    double s[3] = {0, 0, 0};
-    for (int32_t sc = G.cell0[a]; sc < G.cell0[a + 1]; ++sc)
-      for (int q = 0; q < 3; ++q) s[q] += g.ccen[3 * (int64_t)order[sc] + q];
-    double n = G.cell0[a + 1] - G.cell0[a];
-    for (int q = 0; q < 3; ++q) G.orig[3 * a + q] = std::ldexp(std::nearbyint(std::ldexp(s[q] / n, 15)), -15);
-  }
+  group_origins(g, order, G.cell0, G.orig);
   // group pairs: every cell pair maps to (group(sc), group(sd), img) with group(sc) <= group(sd)
   // since groups are consecutive ranges of the sorted order; (A, A, 0) is the self entry.
   std::vector<int64_t> pstart(ng + 1, 0);
@@ -1043,7 +1053,7 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
 static constexpr int32_t kRunGap = 2;
 
 int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
-                const std::vector<CellPair> &pairs, bool whole_groups, double density, double target, Neigh &N) {
+                const std::vector<CellPair> &pairs, double density, double target, Neigh &N) {
   const int64_t nc = g.nc;
   cut_groups(g, order, split_depth, density, target, N.cell0, N.cut);
   const int64_t ng = N.ng = (int64_t)N.cell0.size();
@@ -1051,17 +1061,7 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
   std::vector<int32_t> of_cell(nc);
   for (int64_t a = 0; a < ng; ++a)
     for (int64_t s = N.cell0[a]; s < N.cell0[a + 1]; ++s) of_cell[s] = (int32_t)a;
-  // origins: mean of member centroids rounded to a multiple of 2^-15
-  N.orig.assign(3 * ng, 0.0);
-  parallel_for(ng, [&](int64_t b, int64_t e, int) {
-    for (int64_t a = b; a < e; ++a) {
-      double s[3] = {0, 0, 0};
-      for (int32_t sc = N.cell0[a]; sc < N.cell0[a + 1]; ++sc)
-        for (int q = 0; q < 3; ++q) s[q] += g.ccen[3 * (int64_t)order[sc] + q];
-      const double n = N.cell0[a + 1] - N.cell0[a];
-      for (int q = 0; q < 3; ++q) N.orig[3 * a + q] = std::ldexp(std::nearbyint(std::ldexp(s[q] / n, 15)), -15);
-    }
-  });
+  group_origins(g, order, N.cell0, N.orig);
   std::vector<int64_t> pstart(ng + 1, 0);
   {
     int64_t p = 0;
@@ -1139,15 +1139,6 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
           R.push_back(CellRun{d, d + 1, (int32_t)E.size() - 1, 0});
         }
       }
-      if (whole_groups) {
-        // The vertex predicate does not list every cell pair in range, so a cell that one group reads need not
-        // have the other side's cells read back: whole groups are read instead, which is symmetric.
-        R.clear();
-        for (size_t k = 0; k < E.size(); ++k) {
-          const int32_t B = (int32_t)(E[k] & 0x7FFFFFFF);
-          R.push_back(CellRun{N.cell0[B], N.cell0[B + 1], (int32_t)k, 0});
-        }
-      }
       std::vector<int64_t>().swap(lists[a]);
     }
   });
@@ -1171,6 +1162,131 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
         N.e_B[k] = B;
         N.e_code[k] = (int8_t)code;
         ++k;
+      }
+      CellRun *o = N.runs.data() + N.run_off[a];
+      for (CellRun r : runs[a]) {
+        r.e += (int32_t)N.e_off[a];
+        *o++ = r;
+      }
+    }
+  });
+  N.reach = group_reach(g, order, N.cell0, N.orig, N.e_off, N.e_B, [&](int64_t k) { return (int)N.e_code[k]; });
+  return AICA_OK;
+}
+
+int build_neigh_masked(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
+                       const Groups &G, double density, double target, Neigh &N) {
+  const int64_t nc = g.nc;
+  cut_groups(g, order, split_depth, density, target, N.cell0, N.cut);
+  const int64_t ng = N.ng = (int64_t)N.cell0.size();
+  N.cell0.push_back((int32_t)nc);
+  std::vector<int32_t> of_cell(nc);
+  for (int64_t a = 0; a < ng; ++a)
+    for (int64_t s = N.cell0[a]; s < N.cell0[a + 1]; ++s) of_cell[s] = (int32_t)a;
+  group_origins(g, order, N.cell0, N.orig);
+  auto code_of = [&](int64_t e) { return img_code(G.e_img[3 * e], G.e_img[3 * e + 1], G.e_img[3 * e + 2]); };
+  // needed cells of each half-list entry, and the entries that refer to each half group
+  const int64_t HE = G.e_off[G.ng];
+  std::vector<int64_t> n_off(HE + 1, 0), r_off(G.ng + 1, 0);
+  std::vector<int32_t> of_entry(HE);
+  for (const int32_t e : G.nl_e) n_off[e + 1]++;
+  for (int64_t e = 0; e < HE; ++e) n_off[e + 1] += n_off[e];
+  for (int64_t e = 0; e < HE; ++e) r_off[G.e_B[e] + 1]++;
+  for (int64_t h = 0; h < G.ng; ++h) r_off[h + 1] += r_off[h];
+  std::vector<int64_t> r_e(HE), fill(r_off.begin(), r_off.end() - 1);
+  for (int64_t h = 0; h < G.ng; ++h)
+    for (int64_t e = G.e_off[h]; e < G.e_off[h + 1]; ++e) {
+      of_entry[e] = (int32_t)h;
+      r_e[fill[G.e_B[e]]++] = e;
+    }
+  using Bits = std::vector<uint64_t>;  // over a group's own cells
+  struct Block {                       // the cells of one half group through one image
+    Bits base;                         // own cells that pair with all of them
+    std::vector<int64_t> fwd;          // half-list entries whose group pairs with the cells they need
+  };
+  struct Item {
+    bool other;  // not the group's own
+    int32_t code, cell, entry;
+  };
+  std::vector<std::vector<std::pair<int32_t, int8_t>>> ents(ng);  // (j-group, image code)
+  std::vector<std::vector<Bits>> cols(ng);
+  std::vector<std::vector<CellRun>> runs(ng);
+  parallel_for(ng, [&](int64_t b, int64_t end, int) {
+    for (int64_t a = b; a < end; ++a) {
+      const int32_t c0 = N.cell0[a], c1 = N.cell0[a + 1];
+      const size_t nw = ((size_t)(c1 - c0) + 63) / 64;
+      auto set = [&](Bits &v, int32_t c) { v[(c - c0) / 64] |= 1ull << ((c - c0) % 64); };
+      auto set_group = [&](Bits &v, int32_t h) {
+        for (int32_t c = std::max(c0, G.cell0[h]); c < std::min(c1, G.cell0[h + 1]); ++c) set(v, c);
+      };
+      std::map<std::pair<int32_t, int32_t>, Block> blocks;  // by (image code, half group)
+      auto block = [&](int32_t code, int32_t h) -> Block & {
+        Block &k = blocks[{code, h}];
+        if (k.base.empty()) k.base.assign(nw, 0);
+        return k;
+      };
+      for (int32_t h = G.of_cell[c0]; h <= G.of_cell[c1 - 1]; ++h) {
+        for (int64_t e = G.e_off[h]; e < G.e_off[h + 1]; ++e) {
+          if (G.e_B[e] == h && code_of(e) == 13) set_group(block(13, h).base, h);
+          else block(code_of(e), G.e_B[e]).fwd.push_back(e);
+        }
+        for (int64_t r = r_off[h]; r < r_off[h + 1]; ++r) {
+          const int64_t e = r_e[r];
+          if (of_entry[e] == h && code_of(e) == 13) continue;
+          for (int64_t k = n_off[e]; k < n_off[e + 1]; ++k)
+            if (G.nl_d[k] >= c0 && G.nl_d[k] < c1) set(block(26 - code_of(e), of_entry[e]).base, G.nl_d[k]);
+        }
+      }
+      std::map<std::pair<std::pair<int32_t, int32_t>, Bits>, int32_t> index;  // entry of (code, j-group) and own cells
+      std::vector<Item> items;
+      for (auto &kb : blocks) {
+        const int32_t code = kb.first.first, h = kb.first.second;
+        const Block &k = kb.second;
+        for (int32_t d = G.cell0[h]; d < G.cell0[h + 1]; ++d) {
+          Bits col = k.base;
+          for (const int64_t e : k.fwd)
+            if (std::binary_search(G.nl_d.begin() + n_off[e], G.nl_d.begin() + n_off[e + 1], d)) set_group(col, of_entry[e]);
+          if (std::all_of(col.begin(), col.end(), [](uint64_t w) { return w == 0; })) continue;
+          const auto it = index.insert({{{code, of_cell[d]}, col}, (int32_t)ents[a].size()});
+          if (it.second) {
+            ents[a].push_back({of_cell[d], (int8_t)code});
+            cols[a].push_back(col);
+          }
+          items.push_back({!(code == 13 && d >= c0 && d < c1), code, d, it.first->second});
+        }
+      }
+      std::sort(items.begin(), items.end(), [](const Item &x, const Item &y) {
+        return x.other != y.other ? y.other : x.code != y.code ? x.code < y.code : x.cell < y.cell;
+      });
+      for (const Item &t : items) {
+        if (!runs[a].empty() && runs[a].back().e == t.entry && runs[a].back().d1 == t.cell) runs[a].back().d1++;
+        else runs[a].push_back(CellRun{t.cell, t.cell + 1, t.entry, 0});
+      }
+    }
+  });
+  N.e_off.assign(ng + 1, 0);
+  N.run_off.assign(ng + 1, 0);
+  N.i_off.assign(ng, 0);
+  int64_t words = 0;
+  for (int64_t a = 0; a < ng; ++a) {
+    N.e_off[a + 1] = N.e_off[a] + (int64_t)ents[a].size();
+    N.run_off[a + 1] = N.run_off[a] + (int64_t)runs[a].size();
+    N.i_off[a] = words;
+    words += (((int64_t)ents[a].size() + 31) / 32) * (N.cell0[a + 1] - N.cell0[a]);
+  }
+  if (N.e_off[ng] >= (1LL << 31)) return fail(AICA_E_NOMEM, "too many group pairs");
+  N.e_B.resize(N.e_off[ng]);
+  N.e_code.resize(N.e_off[ng]);
+  N.runs.resize(N.run_off[ng]);
+  N.i_mask.assign(words, 0);
+  parallel_for(ng, [&](int64_t b, int64_t end, int) {
+    for (int64_t a = b; a < end; ++a) {
+      const int64_t rw = ((int64_t)ents[a].size() + 31) / 32;
+      for (size_t k = 0; k < ents[a].size(); ++k) {
+        N.e_B[N.e_off[a] + k] = ents[a][k].first;
+        N.e_code[N.e_off[a] + k] = ents[a][k].second;
+        for (int64_t c = 0; c < N.cell0[a + 1] - N.cell0[a]; ++c)
+          if ((cols[a][k][c / 64] >> (c % 64)) & 1) N.i_mask[N.i_off[a] + c * rw + k / 32] |= 1u << (k % 32);
       }
       CellRun *o = N.runs.data() + N.run_off[a];
       for (CellRun r : runs[a]) {

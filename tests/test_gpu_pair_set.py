@@ -113,3 +113,81 @@ def test_pairs_at_the_cutoff(A, monkeypatch, system, targets, precision, pos_dty
 def test_pairs_at_the_cutoff_of_large_systems(A, shape, precision, width):
     mesh, x = _box(shape, np.random.default_rng(102), width)
     _agree(A, mesh, x, precision, "float64", width)
+
+
+def _dense(n_mesh, L, k, seed):
+    """A strongly jittered mesh (some cells are in range only between face or edge interiors) and a dense jittered
+    lattice of k^3 molecules (multiples of 2^-15)."""
+    rng = np.random.default_rng(seed)
+    nodes = W.uniform_nodes(L, n_mesh)
+    mesh = W.hex_mesh(nodes, nodes, nodes, periodic_axes=(0, 1, 2))
+    mesh = W.jitter_interior(mesh, nodes, nodes, nodes, 0.3, rng)
+    mesh = W.renumber_cells(mesh, rng.permutation(mesh.n_cells))
+    g = np.stack(np.meshgrid(*[np.arange(k)] * 3, indexing="ij"), -1).reshape(-1, 3) + 0.5
+    x = W.qround((g + rng.uniform(-0.35, 0.35, g.shape)) * (L / k))
+    return mesh, x
+
+
+# the vertex predicate lists fewer cell pairs than are in range: which pairs inside the cut-off it leaves out must not
+# depend on the call
+@pytest.mark.parametrize("n_mesh,L,k,seed", [(6, 12.0, 18, 0), (12, 24.0, 30, 4), (20, 40.0, 37, 0), (20, 40.0, 37, 1)])
+def test_vertex_predicate_has_one_pair_set(A, n_mesh, L, k, seed):
+    import torch
+    mesh, x = _dense(n_mesh, L, k, seed)
+    n, eps, sig = len(x), 1.0, 0.6
+    d = A.DIL(mesh, RC, predicate="vertex")
+    sets = {}
+    for prec in ("fp64", "fp32"):
+        t = torch.tensor(x, dtype=getattr(torch, "float" + prec[2:]), device="cuda")
+        print(f"vertex predicate: n={n} {prec}", flush=True)
+        A.aica_bin(d, t)
+        F, uw, npairs = A.aica_forces(d, t, None, [eps], [sig], precision=prec)
+        gx, ge, gs = A.aica_forces_adjoint(d, t, torch.zeros_like(F), 1.0, None, [eps], [sig], precision=prec)
+        P = sets[prec] = A.aica_pairs_export(d, t, precision=prec)
+        counts = A.aica_pair_counts(d, t, precision=prec).cpu().numpy()
+        dx = x[P[:, 0]] - x[P[:, 1]] - L * P[:, 2:]
+        s = (dx ** 2).sum(1)
+        s6 = (sig * sig / s) ** 3
+        assert int(npairs.item()) == len(P)
+        assert np.array_equal(counts, np.bincount(P[:, :2].ravel(), minlength=n))
+        # with G = 0 and gamma = 1, dL/deps is U / eps and dL/dx is -F: sums over the pairs of FP64 terms
+        u = 4.0 * (s6 * s6 - s6)
+        assert abs(ge[0].item() - u.sum()) <= 1e-12 * np.abs(u).sum()
+        f = (24.0 * (2.0 * s6 * s6 - s6) / s)[:, None] * dx
+        Fr = np.stack([np.bincount(P[:, 0], f[:, q], n) - np.bincount(P[:, 1], f[:, q], n) for q in range(3)], 1)
+        # (molecules nearly touch: FP32 forces are not compared; the adjoint's terms and sums are FP64 in both precisions,
+        # rounded once)
+        rms = np.sqrt((Fr ** 2).sum(1).mean())
+        if prec == "fp64":
+            assert np.abs(F.cpu().numpy() - Fr).max() <= 1e-12 * rms
+        once = 0.0 if prec == "fp64" else 2.0 ** -24 * np.abs(Fr)
+        assert np.all(np.abs(gx.double().cpu().numpy() + Fr) <= 1e-12 * rms + once)
+    assert np.array_equal(sets["fp32"], sets["fp64"])
+
+
+# the same across a rotated side and with mixtures: with G = 0 and gamma = 1 the adjoint gives -F, and U as the sum of
+# eps dL/deps (U is of first degree in eps)
+@pytest.mark.parametrize("nsp", [1, 2, 3])
+def test_vertex_predicate_adjoint_is_that_of_the_forces(A, nsp):
+    import torch
+    wl = W.wedge(seed=8, r0=10.0, r1=24.0, Lz=9.0, nr=9, nphi=6, nz=6, density=0.8, jitter=0.3)
+    n, eps, sig = wl.n, np.array([1.0, 0.6, 0.8])[:nsp], np.array([1.0, 0.9, 0.95])[:nsp]
+    sp = torch.tensor(np.random.default_rng(4).integers(0, nsp, n).astype(np.int32), device="cuda")
+    d, dc = A.DIL(wl.mesh, RC, predicate="vertex"), A.DIL(wl.mesh, RC)
+    assert d.info()["n_dil"] < dc.info()["n_dil"]
+    print(f"vertex predicate, sector: n={n} species={nsp}", flush=True)
+    out = {}
+    for prec in ("fp64", "fp32"):
+        t = torch.tensor(wl.x, dtype=getattr(torch, "float" + prec[2:]), device="cuda")
+        A.aica_bin(d, t)
+        F, uw, npairs = A.aica_forces(d, t, sp, eps, sig, precision=prec)
+        gx, ge, gs = A.aica_forces_adjoint(d, t, torch.zeros_like(F), 1.0, sp, eps, sig, precision=prec)
+        assert int(npairs.item()) == len(A.aica_pairs_export(d, t, precision=prec))
+        out[prec] = [v.double().cpu().numpy() for v in (F, uw, gx, ge)]
+    F, uw, gx, ge = out["fp64"]
+    rms = np.sqrt((F ** 2).sum(1).mean())
+    assert np.abs(gx + F).max() <= 1e-12 * rms
+    assert abs((eps * ge).sum() - uw[0]) <= 1e-12 * abs(uw[0])
+    F, uw, gx, ge = out["fp32"]  # the bars of the FP32 path: forces 1e-5, adjoint 1e-6
+    assert np.abs(gx + F).max() <= 1.1e-5 * rms
+    assert abs((eps * ge).sum() - out["fp64"][1][0]) <= 1e-6 * abs(out["fp64"][1][0])
