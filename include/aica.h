@@ -123,7 +123,8 @@ int aica_build_dil_ex(const aica_mesh *mesh, double rcut, double guard, int32_t 
  * across its faces, then a background grid.  The answer does not depend on
  * the history (every route certifies the same cell).  A cell may hold any
  * number of molecules.  Synchronises the stream once, to read the unlocated
- * and reaction-slot counts.
+ * and reaction-slot counts, and once more before it rebuilds the interaction
+ * lists (first call, and an n that changes the groups).
  * Errors: AICA_E_INVAL (n < 0 or n >= 2^28 - 1, null, bad dtype),
  * AICA_E_UNLOCATED (the count is in aica_last_error), AICA_E_NOMEM (more than
  * 2^31 reaction records), AICA_E_HIP. */

@@ -1421,7 +1421,7 @@ static int make_neigh(aica_dil *h, double density, double target) {
 // 188, 28,000 191 and 190, 31,999 of five species 180 and 185; 40,000 232 and 203; with 32 no size is faster).  They are kept while n leaves the cuts as they are: a program whose molecule
 // count changes from step to step rebuilt them at every binning (117 ms of host work at 371,896 molecules, 1.6 s at 6.7
 // million).
-static int ensure_groups(aica_dil *h, int64_t n) {
+static int ensure_groups(aica_dil *h, int64_t n, hipStream_t st) {
   const double density = (double)n / h->geo.total_volume;
   double target = 64.0;  // largest expected occupancy of a group (k-d subtree; measured best on the channel)
   if (const char *e = getenv("AICA_GROUP_TARGET")) target = std::max(1.0, atof(e));
@@ -1432,6 +1432,9 @@ static int ensure_groups(aica_dil *h, int64_t n) {
   const bool nb_keep =
       h->neigh_ready && h->nb.cut.holds(density, nb_target) && (keep || h->predicate != AICA_DIL_VERTEX);
   if (keep && nb_keep) return AICA_OK;
+  // the lists are overwritten in place: work of the last steps that still reads them has to end first (the copies are not
+  // ordered with a non-blocking stream)
+  HIPCHK(hipStreamSynchronize(st));
   auto t0 = std::chrono::steady_clock::now();
   int rc;
   if (!keep && (rc = make_groups(h, density, target))) return rc;
@@ -1529,7 +1532,7 @@ int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, voi
     if ((rc = upload_geometry(h))) return rc;
     h->geometry_on_device = true;
   }
-  rc = ensure_groups(h, n);
+  rc = ensure_groups(h, n, st);
   if (rc) return rc;
   const int64_t nc = h->geo.nc;
   if (!h->host_status && hipHostMalloc((void **)&h->host_status, 8 * (8 + kRouteSlots)) != hipSuccess) {
