@@ -1741,19 +1741,22 @@ static int launch_pair(aica_dil *h, const ForceWs &ws, const LJTab &tab, bool co
       AICA_LAUNCH_S(MIX, COMP, ROT, false);              \
     }                                                    \
   } while (0)
-#define AICA_LAUNCH(MIX, COMP) AICA_LAUNCH_R(MIX, COMP, false)
-  if (rot) {  // rotating referral: compensated sums always (the variants with a rotation are built once)
-    if (nsp == 1) AICA_LAUNCH_R(0, true, true);
-    else if (nsp == 2) AICA_LAUNCH_R(1, true, true);
-    else AICA_LAUNCH_R(2, true, true);
-  } else if (MODE == 1 || (comp && sizeof(T) == 4)) {  // compensated sums exist in FP32 only
-    if (nsp == 1) AICA_LAUNCH(0, true);
-    else if (nsp == 2) AICA_LAUNCH(1, true);
-    else AICA_LAUNCH(2, true);
+#define AICA_LAUNCH(COMP, ROT)                 \
+  do {                                         \
+    if (nsp == 1) AICA_LAUNCH_R(0, COMP, ROT); \
+    else if (nsp == 2) AICA_LAUNCH_R(1, COMP, ROT); \
+    else AICA_LAUNCH_R(2, COMP, ROT);          \
+  } while (0)
+  if constexpr (MODE == 1) {  // the pairs are the same whatever the species (compensation is of no account)
+    if (rot) AICA_LAUNCH_R(0, true, true);
+    else AICA_LAUNCH_R(0, true, false);
+  } else if (rot) {  // rotating referral: compensated sums always (the variants with a rotation are built once)
+    AICA_LAUNCH(true, true);
+  } else if constexpr (sizeof(T) == 4) {  // compensated sums exist in FP32 only
+    if (comp) AICA_LAUNCH(true, false);
+    else AICA_LAUNCH(false, false);
   } else {
-    if (nsp == 1) AICA_LAUNCH(0, false);
-    else if (nsp == 2) AICA_LAUNCH(1, false);
-    else AICA_LAUNCH(2, false);
+    AICA_LAUNCH(false, false);
   }
 #undef AICA_LAUNCH
 #undef AICA_LAUNCH_R
@@ -1962,8 +1965,9 @@ static int forces_impl(aica_dil *h, const ForceWs &ws, const void *pos_dev, cons
   {
     ProfScope ps(h, "finalize", st);
     if (!full && n > 0 && forces_dev) {
-      if (comp && sizeof(T) == 4)
-        launch_finalize<T, true>(h, ws, forces_dev, st);
+      constexpr bool C = sizeof(T) == 4;  // compensated sums exist in FP32 only
+      if (comp)
+        launch_finalize<T, C>(h, ws, forces_dev, st);
       else
         launch_finalize<T, false>(h, ws, forces_dev, st);
     }
