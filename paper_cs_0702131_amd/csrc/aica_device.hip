@@ -1298,11 +1298,13 @@ static int make_groups(aica_dil *h, double density, double target) {
   // Entry offsets: a j of group B at xm relative to orig_B is referred into A's frame at R xm + o with
   // o = T(orig_B) - orig_A (R = I and o = orig_B + t - orig_A for a translation).  The fourth component
   // holds the image code, plus kRotFlag when the image has a rotation (whose R the kernels look up).
+  const std::array<Xf, 27> image = image_table(h->geo);
   parallel_for(G.ng, [&](int64_t b, int64_t en, int) {
     for (int64_t A = b; A < en; ++A)
       for (int64_t e = G.e_off[A]; e < G.e_off[A + 1]; ++e) {
         const int64_t B = G.e_B[e];
-        const Xf T = image_transform(h->geo, G.e_img[3 * e], G.e_img[3 * e + 1], G.e_img[3 * e + 2]);
+        const int img = 9 * (G.e_img[3 * e] + 1) + 3 * (G.e_img[3 * e + 1] + 1) + (G.e_img[3 * e + 2] + 1);
+        const Xf &T = image[img];
         double o[3];
         if (T.rot) {
           double tb[3];
@@ -1311,20 +1313,15 @@ static int make_groups(aica_dil *h, double density, double target) {
         } else {
           for (int q = 0; q < 3; ++q) o[q] = G.orig[3 * B + q] + T.y[q] - G.orig[3 * A + q];
         }
-        const int code = 9 * (G.e_img[3 * e] + 1) + 3 * (G.e_img[3 * e + 1] + 1) + (G.e_img[3 * e + 2] + 1) +
-                         (T.rot ? kRotFlag : 0);
+        const int code = img + (T.rot ? kRotFlag : 0);
         v32[e] = make_float4((float)o[0], (float)o[1], (float)o[2], __builtin_bit_cast(float, code));
         v64[e] = make_double4(o[0], o[1], o[2], __builtin_bit_cast(double, (int64_t)code));
       }
   });
   if (h->geo.has_rot) {  // R of every image code (the identity for translations)
     std::vector<double> r64(27 * 9);
-    for (int code = 0; code < 27; ++code) {
-      const Xf T = image_transform(h->geo, code / 9 - 1, (code / 3) % 3 - 1, code % 3 - 1);
-      for (int i = 0; i < 9; ++i) {
-        r64[9 * code + i] = T.R[i];
-      }
-    }
+    for (int code = 0; code < 27; ++code)
+      for (int i = 0; i < 9; ++i) r64[9 * code + i] = image[code].R[i];
     if ((rc = upload(h->d_rot64, r64))) return rc;
   }
   if ((rc = upload(h->d_g_cell0, G.cell0))) return rc;
@@ -1361,12 +1358,13 @@ static int make_neigh(aica_dil *h, double density, double target) {
   const int64_t NE = N.e_off[N.ng];
   std::vector<float4> v32(NE);
   std::vector<double4> v64(NE);
+  const std::array<Xf, 27> image = image_table(h->geo);
   parallel_for(N.ng, [&](int64_t b, int64_t e, int) {
     for (int64_t a = b; a < e; ++a)
       for (int64_t k = N.e_off[a]; k < N.e_off[a + 1]; ++k) {
         const int64_t B = N.e_B[k];
         const int c = N.e_code[k];
-        const Xf T = image_transform(h->geo, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
+        const Xf &T = image[c];
         double o[3], tb[3] = {0, 0, 0};
         if (T.rot) T.apply(&N.orig[3 * B], tb);
         for (int q = 0; q < 3; ++q)
@@ -1380,10 +1378,7 @@ static int make_neigh(aica_dil *h, double density, double target) {
     std::vector<int32_t> list, turned;
     for (int64_t a = 0; a < N.ng; ++a) {
       bool rot = false;
-      for (int64_t e = N.e_off[a]; e < N.e_off[a + 1] && !rot; ++e) {
-        const int c = N.e_code[e];
-        rot = image_transform(h->geo, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1).rot;
-      }
+      for (int64_t e = N.e_off[a]; e < N.e_off[a + 1] && !rot; ++e) rot = image[N.e_code[e]].rot;
       (rot ? turned : list).push_back((int32_t)a);
     }
     h->nb_plain_groups = (int64_t)list.size();

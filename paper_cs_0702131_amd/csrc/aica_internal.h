@@ -2,6 +2,7 @@
 #pragma once
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cstdint>
 #include <string>
@@ -19,17 +20,18 @@ int fail(int code, const std::string &msg);
 // Number of host worker threads for setup (AICA_THREADS, else OMP_NUM_THREADS, else hardware).
 int host_threads();
 
-// f(begin, end, worker) over [0, n) in dynamically claimed chunks on host_threads() threads.
+// f(begin, end, worker) over [0, n) in dynamically claimed chunks of at least grain on host_threads() threads, or at once
+// where that would be fewer than 16 chunks.
 template <class F>
-void parallel_for(int64_t n, F f) {
+void parallel_for(int64_t n, F f, int64_t grain = 64) {
   const int nt = host_threads();
-  if (n < 1024 || nt == 1) {
+  if (n < 16 * grain || nt == 1) {
     f(0, n, 0);
     return;
   }
   std::vector<std::thread> th;
   std::atomic<int64_t> next(0);
-  const int64_t chunk = std::max<int64_t>(64, n / (nt * 16));
+  const int64_t chunk = std::max<int64_t>(grain, n / (nt * 16));
   for (int t = 0; t < nt; ++t)
     th.emplace_back([&, t]() {
       for (;;) {
@@ -98,6 +100,7 @@ void spatial_order(const Geometry &g, std::vector<int32_t> &order, std::vector<i
 
 // Image n of the periodic directions: T_1^n0 T_2^n1 T_3^n2 (the transforms commute).
 Xf image_transform(const Geometry &g, int n0, int n1, int n2);
+std::array<Xf, 27> image_table(const Geometry &g);  // by image code 9 (n0 + 1) + 3 (n1 + 1) + (n2 + 1)
 
 // Largest coordinate (any axis) of a mesh point or of a first image's shift, summed.
 double coordinate_size(const Geometry &g);

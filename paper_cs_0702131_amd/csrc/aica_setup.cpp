@@ -84,23 +84,27 @@ Xf image_transform(const Geometry &g, int n0, int n1, int n2) {
   return t;
 }
 
+std::array<Xf, 27> image_table(const Geometry &g) {
+  std::array<Xf, 27> T;
+  for (int c = 0; c < 27; ++c) T[c] = image_transform(g, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
+  return T;
+}
+
 double coordinate_size(const Geometry &g) {
   double x = 0, y = 0;
   for (int q = 0; q < 3; ++q) x = std::max({x, std::fabs(g.dom_lo[q]), std::fabs(g.dom_hi[q])});
-  for (int c = 0; c < 27; ++c) {
-    const Xf t = image_transform(g, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
+  for (const Xf &t : image_table(g))
     for (int q = 0; q < 3; ++q) y = std::max(y, std::fabs(t.y[q]));
-  }
   return x + y;
 }
 
 double transform_skew(const Geometry &g) {
   if (!g.has_rot) return 0;  // lattice translations are taken back exactly
   const double size = coordinate_size(g);
+  const std::array<Xf, 27> T = image_table(g);
   double m = 0;
   for (int c = 0; c < 27; ++c) {
-    const Xf t = image_transform(g, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
-    const Xf b = t.then(image_transform(g, 1 - c / 9, 1 - (c / 3) % 3, 1 - c % 3));
+    const Xf b = T[c].then(T[26 - c]);
     for (int i = 0; i < 3; ++i) {
       double v = std::fabs(b.y[i]);
       for (int j = 0; j < 3; ++j) v += std::fabs(b.R[3 * i + j] - (i == j ? 1.0 : 0.0)) * size;
@@ -837,6 +841,41 @@ int build_cell_pairs(const Geometry &g, const std::vector<int32_t> &order, const
 
 // ------------------------------------------------------------------ interaction groups
 
+// The distinct keys (>= 0) of a group, ascending.  Its cell pairs name each about ten times: the repeats are dropped as
+// they come, so that only the distinct ones are sorted.
+class KeySet {
+ public:
+  void clear() {
+    std::fill(slot_.begin(), slot_.end(), -1);
+    keys_.clear();
+  }
+  void add(int64_t key) {
+    if (2 * keys_.size() >= slot_.size()) grow();
+    if (put(key)) keys_.push_back(key);
+  }
+  const std::vector<int64_t> &sorted() {
+    std::sort(keys_.begin(), keys_.end());
+    return keys_;
+  }
+
+ private:
+  bool put(int64_t key) {
+    const size_t mask = slot_.size() - 1;
+    size_t k = (size_t)(((uint64_t)key * 0x9E3779B97F4A7C15ull) >> 32) & mask;
+    while (slot_[k] >= 0) {
+      if (slot_[k] == key) return false;
+      k = (k + 1) & mask;
+    }
+    slot_[k] = key;
+    return true;
+  }
+  void grow() {
+    slot_.assign(std::max<size_t>(1024, 2 * slot_.size()), -1);
+    for (const int64_t key : keys_) put(key);
+  }
+  std::vector<int64_t> slot_, keys_;
+};
+
 static void cut_groups(const Geometry &g, const std::vector<int32_t> &order, const std::vector<uint8_t> &split_depth,
                        double density, double target, std::vector<int32_t> &cell0, GroupCut &cut) {
   const int64_t nc = g.nc;
@@ -875,6 +914,9 @@ static void cut_groups(const Geometry &g, const std::vector<int32_t> &order, con
   cut.whole_vol = whole_vol;
 }
 
+// Groups per chunk of the loops that build lists: a group has some thousand cell pairs.
+static constexpr int64_t kListGrain = 16;
+
 // Origins: mean of member centroids rounded to a multiple of 2^-15.
 static void group_origins(const Geometry &g, const std::vector<int32_t> &order, const std::vector<int32_t> &cell0,
                           std::vector<double> &orig) {
@@ -897,8 +939,7 @@ static double group_reach(const Geometry &g, const std::vector<int32_t> &order, 
                           const std::vector<double> &orig, const std::vector<int64_t> &e_off,
                           const std::vector<int32_t> &e_B, F code_of) {
   const int64_t ng = (int64_t)cell0.size() - 1;
-  Xf T[27];
-  for (int c = 0; c < 27; ++c) T[c] = image_transform(g, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1);
+  const std::array<Xf, 27> T = image_table(g);
   std::vector<double> ext(ng, 0.0);  // the group's box about its origin
   parallel_for(ng, [&](int64_t b, int64_t e, int) {
     for (int64_t a = b; a < e; ++a)
@@ -949,21 +990,21 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
   }
   std::vector<std::vector<int64_t>> lists(ng);  // key = B * 32 + code
   parallel_for(ng, [&](int64_t b, int64_t e, int) {
+    KeySet keys;
     for (int64_t a = b; a < e; ++a) {
-      std::vector<int64_t> &L = lists[a];
-      L.push_back(a * 32 + 13);
+      keys.clear();
+      keys.add(a * 32 + 13);
       for (int64_t p = pstart[a]; p < pstart[a + 1]; ++p) {
         const CellPair &cp = pairs[p];
         int64_t B = G.of_cell[cp.sd];
         int code = img_code(cp.img[0], cp.img[1], cp.img[2]);
         if (B == a && code == 13) continue;
         if (B == a && code < 13) code = 26 - code;
-        L.push_back(B * 32 + code);
+        keys.add(B * 32 + code);
       }
-      std::sort(L.begin(), L.end());
-      L.erase(std::unique(L.begin(), L.end()), L.end());
+      lists[a] = keys.sorted();
     }
-  });
+  }, kListGrain);
   G.e_off.assign(ng + 1, 0);
   for (int64_t a = 0; a < ng; ++a) G.e_off[a + 1] = G.e_off[a] + (int64_t)lists[a].size();
   const int64_t E = G.e_off[ng];
@@ -987,9 +1028,11 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
   // or, for A == B and a negative image, by entry (A, A, -img) with j in sc.
   std::vector<std::vector<int64_t>> nlists(ng);  // key = entry * 2^31 + j-cell
   parallel_for(ng, [&](int64_t b, int64_t e, int) {
+    KeySet keys;
     for (int64_t a = b; a < e; ++a) {
-      std::vector<int64_t> &L = nlists[a];
+      keys.clear();
       const int64_t eb = G.e_off[a], ee = G.e_off[a + 1];
+      int64_t last_key = -1, last_entry = 0;
       auto find_entry = [&](int32_t B, int code) -> int64_t {
         // entries of A are sorted by (B, code)
         int64_t lo = eb, hi = ee;
@@ -1012,13 +1055,15 @@ int build_groups(const Geometry &g, const std::vector<int32_t> &order, const std
           code = 26 - code;
           jcell = cp.sc;
         }
-        const int64_t en = find_entry(B, code);
-        L.push_back(en * (1LL << 31) + jcell);
+        if ((int64_t)B * 32 + code != last_key) {
+          last_key = (int64_t)B * 32 + code;
+          last_entry = find_entry(B, code);
+        }
+        keys.add(last_entry * (1LL << 31) + jcell);
       }
-      std::sort(L.begin(), L.end());
-      L.erase(std::unique(L.begin(), L.end()), L.end());
+      nlists[a] = keys.sorted();
     }
-  });
+  }, kListGrain);
   G.nl_off.assign(ng + 1, 0);
   for (int64_t a = 0; a < ng; ++a) G.nl_off[a + 1] = G.nl_off[a] + (int64_t)nlists[a].size();
   const int64_t NL = G.nl_off[ng];
@@ -1081,7 +1126,7 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
   std::vector<std::vector<int64_t>> lists(ng);
   std::vector<std::vector<Rev>> rev(ng);
   parallel_for(ng, [&](int64_t b, int64_t e, int) {
-    std::vector<int64_t> L;
+    KeySet L;
     std::vector<Rev> R;
     for (int64_t a = b; a < e; ++a) {
       L.clear();
@@ -1091,16 +1136,14 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
         const int32_t B = of_cell[cp.sd];
         const int code = img_code(cp.img[0], cp.img[1], cp.img[2]);
         if (B == a && code == 13) continue;
-        L.push_back(key_of(code, cp.sd));
+        L.add(key_of(code, cp.sd));
         const Rev r{B, cp.sc, (int8_t)(26 - code)};
         if (R.empty() || R.back().B != r.B || R.back().cell != r.cell || R.back().code != r.code) R.push_back(r);
       }
-      std::sort(L.begin(), L.end());
-      L.erase(std::unique(L.begin(), L.end()), L.end());
-      lists[a] = L;
+      lists[a] = L.sorted();
       rev[a] = R;
     }
-  });
+  }, kListGrain);
   {
     std::vector<int64_t> roff(ng + 1, 0);
     for (int64_t a = 0; a < ng; ++a)
@@ -1118,7 +1161,7 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
         std::sort(L.begin(), L.end());
         L.erase(std::unique(L.begin(), L.end()), L.end());
       }
-    });
+    }, kListGrain);
   }
   // entries (code, B) and runs of cells: the keys are sorted by (code, cell), so by (code, B, cell)
   std::vector<std::vector<int64_t>> ents(ng);
@@ -1141,7 +1184,7 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
       }
       std::vector<int64_t>().swap(lists[a]);
     }
-  });
+  }, kListGrain);
   N.e_off.assign(ng + 1, 0);
   N.run_off.assign(ng + 1, 0);
   for (int64_t a = 0; a < ng; ++a) {
@@ -1169,7 +1212,7 @@ int build_neigh(const Geometry &g, const std::vector<int32_t> &order, const std:
         *o++ = r;
       }
     }
-  });
+  }, kListGrain);
   N.reach = group_reach(g, order, N.cell0, N.orig, N.e_off, N.e_B, [&](int64_t k) { return (int)N.e_code[k]; });
   return AICA_OK;
 }
@@ -1263,7 +1306,7 @@ int build_neigh_masked(const Geometry &g, const std::vector<int32_t> &order, con
         else runs[a].push_back(CellRun{t.cell, t.cell + 1, t.entry, 0});
       }
     }
-  });
+  }, kListGrain);
   N.e_off.assign(ng + 1, 0);
   N.run_off.assign(ng + 1, 0);
   N.i_off.assign(ng, 0);
@@ -1294,7 +1337,7 @@ int build_neigh_masked(const Geometry &g, const std::vector<int32_t> &order, con
         *o++ = r;
       }
     }
-  });
+  }, kListGrain);
   N.reach = group_reach(g, order, N.cell0, N.orig, N.e_off, N.e_B, [&](int64_t k) { return (int)N.e_code[k]; });
   return AICA_OK;
 }
