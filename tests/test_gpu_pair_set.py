@@ -33,11 +33,11 @@ def _separations(m, rng, width):
     return RC * (1.0 + e)[:, None] * u
 
 
-def _box(shape, rng, width):
+def _box(shape, rng, width, cells=None):
     """Pairs on a grid of sites in a periodic box whose x and y periods are no multiples of a power of two; rows k and
-    m + k are a pair."""
+    m + k are a pair.  A mesh cell per site by default."""
     L = np.array([SITE * s for s in shape]) + np.array([1.0 / 7.0, 1.0 / 11.0, 0.0])
-    mesh = W.hex_mesh(*[W.uniform_nodes(L[k], shape[k]) for k in range(3)], periodic_axes=(0, 1, 2))
+    mesh = W.hex_mesh(*[W.uniform_nodes(L[k], (cells or shape)[k]) for k in range(3)], periodic_axes=(0, 1, 2))
     g = np.stack(np.meshgrid(*[np.arange(s) for s in shape], indexing="ij"), -1).reshape(-1, 3)
     a = (g + 0.5 + rng.uniform(-0.04, 0.04, g.shape)) * (L / shape)
     a[:, 0] -= 0.5 * L[0] / shape[0]  # the first layer of sites lies on the periodic side
@@ -112,6 +112,14 @@ def test_pairs_at_the_cutoff(A, monkeypatch, system, targets, precision, pos_dty
 @pytest.mark.parametrize("precision,width", [("fp64", 2e-14), ("fp32", 2e-5)])
 def test_pairs_at_the_cutoff_of_large_systems(A, shape, precision, width):
     mesh, x = _box(shape, np.random.default_rng(102), width)
+    _agree(A, mesh, x, precision, "float64", width)
+
+
+# cells thousands of cut-offs wide: FP32 rounds their molecules' positions so coarsely that the box test and the search
+# need the band's radius
+@pytest.mark.parametrize("precision,width", [("fp64", 2e-12), ("fp32", 1e-3)])
+def test_pairs_at_the_cutoff_in_wide_cells(A, precision, width):
+    mesh, x = _box((1000, 2, 2), np.random.default_rng(103), width, cells=(2, 1, 1))
     _agree(A, mesh, x, precision, "float64", width)
 
 
