@@ -114,8 +114,8 @@ struct aica_dil {
   DBuf d_nb_cell0, d_nb_run_off, d_nb_runs, d_nb_vec32, d_nb_vec64, d_nb_orig, d_nb_eoff, d_nb_ioff, d_nb_imask;
   DBuf d_of_cell, d_half;       // the half lists' group of each sorted cell; HalfFrames
   // a pair vector formed in the frames of the full lists differs per axis from that of the half lists by at most
-  // (half an ulp of the compute type) * frame_reach + frame_err
-  double frame_reach = 0, frame_err = 0;
+  // (half an ulp of the compute type) * frame_reach (FP32, FP64) + frame_err
+  double frame_reach[2] = {0, 0}, frame_err = 0;
   DBuf d_box;                   // [groups][6] box of each group's molecules in its frame (compute type)
   // rotating referral: the groups of the full lists without a turned entry, then those with one
   DBuf d_nb_glist;
@@ -235,7 +235,7 @@ constexpr int kPl = 24;
 
 // The FP32 tests of one molecule by a group of 32 lanes, a boundary triangle (and its tetrahedron) per lane: the lanes
 // read a record in a few wide loads and no lane walks the faces in turn.  With the fixed stride of the records a cell
-// has at most 7 faces and 24 triangles.
+// has at most 7 faces and 26 triangles (over kPl of them, its plane test never accepts).
 struct RecLane {
   float f[3], vp[3], vn[3];  // this lane's triangle: face centroid and two consecutive vertices, relative to a
   float pr[3], cc[3];
@@ -647,7 +647,7 @@ __device__ __forceinline__ void scan_tile(const int32_t *count, const int32_t *r
   }
 }
 // Few cells: one block, a run of consecutive cells per thread, read twice (its total, then its offsets).  The loads of a
-// run are all in flight at once: tile after tile, 27,000 cells took 20 us.
+// run are all in flight at once: tile after tile, 13,824 cells took 20 us.
 template <bool HALF>
 __global__ __launch_bounds__(kScanThreads) void k_scan_cells(const int32_t *__restrict__ count,
                                                               const int32_t *__restrict__ rcnt, int64_t n,
@@ -758,11 +758,32 @@ __global__ void k_sort_cells(const int32_t *__restrict__ cell_start, const int32
   perm[r] = v;
 }
 
-// Cleared at the start of a binning: the cells' occupancies and the status words.
-__global__ void k_clear_bin(int32_t *count, int64_t nc, unsigned long long *status, int nstatus) {
+// A binning as the pair kernels read it where they decide a pair close to the cut-off.
+struct BinRef {
+  const void *pos;         // [n][3] as passed by the caller, double if pos64, else float
+  const int32_t *perm;     // caller id of each sorted molecule
+  const int32_t *cell_of;  // its sorted cell
+  int32_t pos64;
+};
+// Group frames of the half lists, in which such a pair is decided, written with the lists; bin by every binning.  In
+// device memory: as arguments of the pair kernels, the pointers would take scalar registers from their loops.
+struct HalfFrames {
+  const int32_t *of_cell;   // group of each sorted cell
+  const double *orig;       // [groups][3]
+  const int64_t *e_off;     // [groups+1] entries, sorted by (j-group, image code)
+  const int32_t *e_B;
+  const float4 *e_vec32;    // offset and image code of each entry
+  const double4 *e_vec64;
+  BinRef bin;
+};
+
+// At the start of a binning: the cells' occupancies and the status words cleared, the frames' reference to the binning.
+__global__ void k_clear_bin(int32_t *count, int64_t nc, unsigned long long *status, int nstatus, HalfFrames *half,
+                            BinRef bin) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < nc) count[i] = 0;
   if (i < nstatus) status[i] = 0;
+  if (i == 0) half->bin = bin;
 }
 
 template <typename T>
@@ -1341,7 +1362,7 @@ static int make_groups(aica_dil *h, double density, double target) {
   if ((rc = upload(h->d_orig, G.orig))) return rc;
   if ((rc = upload(h->d_of_cell, G.of_cell))) return rc;
   const HalfFrames hf{h->d_of_cell.as<int32_t>(), h->d_orig.as<double>(), h->d_e_off.as<int64_t>(), h->d_e_B.as<int32_t>(),
-                      h->d_e_vec32.as<float4>(), h->d_e_vec64.as<double4>()};
+                      h->d_e_vec32.as<float4>(), h->d_e_vec64.as<double4>(), {}};
   if ((rc = upload(h->d_half, std::vector<HalfFrames>{hf}))) return rc;
   h->groups_ready = true;
   return AICA_OK;
@@ -1411,11 +1432,12 @@ static int make_neigh(aica_dil *h, double density, double target) {
   return AICA_OK;
 }
 
-// Both sets of lists, for n molecules.  Full lists: groups of up to 128 expected molecules, or 64 while that leaves fewer
+// Both sets of lists, for n molecules (any call may need either: the full lists decide pairs near rc^2 in the frames of the
+// half lists).  Full lists: groups of up to 128 expected molecules, or 64 while that leaves fewer
 // of them than CUs (a pass of FP64 forces and adjoint, us, 64 against 128: 7,000 molecules 168 and 180, 13,000 166 and
 // 188, 28,000 191 and 190, 31,999 of five species 180 and 185; 40,000 232 and 203; with 32 no size is faster).  They are kept while n leaves the cuts as they are: a program whose molecule
-// count changes from step to step rebuilt them at every binning (117 ms of host work at 371,896 molecules, 1.6 s at 6.7
-// million).
+// count changes from step to step would rebuild them at every binning (107 ms of host work at 371,896 molecules, 1.3 s at
+// 6.7 million).
 static int ensure_groups(aica_dil *h, int64_t n, hipStream_t st) {
   const double density = (double)n / h->geo.total_volume;
   double target = 64.0;  // largest expected occupancy of a group (k-d subtree; measured best on the channel)
@@ -1435,10 +1457,12 @@ static int ensure_groups(aica_dil *h, int64_t n, hipStream_t st) {
   if (!keep && (rc = make_groups(h, density, target))) return rc;
   if (!nb_keep && (rc = make_neigh(h, density, nb_target))) return rc;
   // Half-ulp roundings per axis of a pair vector: a translated one's at most three of the frame's reach (the two
-  // positions in their groups' frames, the offset, the sum), a rotated one's six; and in FP64, at the size of the
-  // coordinates themselves, those of the offsets (T orig_B - orig_A), and how far a transform and its inverse miss.
+  // positions in their groups' frames, the offset, the sum), a rotated one's six in FP64 (in FP32 three: it is formed in
+  // FP64); and in FP64, at the size of the coordinates themselves, those of the offsets (T orig_B - orig_A), and how far
+  // a transform and its inverse miss.
   const bool rot = h->geo.has_rot;
-  h->frame_reach = (rot ? 6.0 : 3.0) * (h->nb.reach + h->grp.reach);
+  h->frame_reach[0] = 3.0 * (h->nb.reach + h->grp.reach);
+  h->frame_reach[1] = (rot ? 6.0 : 3.0) * (h->nb.reach + h->grp.reach);
   h->frame_err = std::ldexp(1.0, -53) * (rot ? 20.0 : 2.5) * coordinate_size(h->geo) + transform_skew(h->geo);
   h->group_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   return AICA_OK;
@@ -1500,11 +1524,13 @@ void aica_dil_free(aica_dil *h) {
 }
 
 // Which lists a force call runs on.  The full lists (k_force: every pair from both sides, no reaction records) take
-// FP64, and FP32 from 200,000 molecules on: 6.7 million molecules take 1.50 ms in place of 2.50 ms (pair kernel) and
-// 0.34 ms (finalize); a step (bin, forces, adjoint) of a mixture of 219,488 took 0.50 ms in place of 0.60 when forces and
-// adjoint had moved and nothing else.  Below that, and with rotating referral, FP32 keeps the half lists: U and W are
-// sums of FP32 terms whose partial sums round to about 1e-9 of the result at 1e4 to 1e5 molecules (at 4e5 across a
-// rotation, where U and W cancel more), and with the half lists they keep the tile-wise partial sums they had.
+// FP64, and FP32 from 200,000 molecules on without rotation: 6.7 million molecules take 1.50 ms in place of 2.50 ms (pair
+// kernel) and 0.34 ms (finalize).  The line is not where the two take the same time.  FP32 bin and forces of a liquid of
+// density 0.8, us, half and full lists: 13,440 molecules 81 and 90, 30,000 103 and 90, 60,000 109 and 102, 100,000 143 and
+// 112, 150,000 173 and 127, 200,000 198 and 135, 400,000 267 and 186.  Nor is it one of accuracy: from 1,000 to 400,000
+// molecules the rms errors against FP64 are the same on either to the second digit (U 2e-8 to 2e-7, W 1.1e-7 to 1.6e-7,
+// F 4.0e-7 to 4.3e-7 of the rms force).  Below it and across rotations the half lists are kept so that U and W stay what
+// they were to the last digits: the lists add FP32 terms in another order, which moves them by about 1e-9.
 // With the vertex predicate both precisions keep them: it does not list every pair in range, and the half lists decide
 // which are left out.
 static bool full_lists(const aica_dil *h, int64_t n, int tsize) {
@@ -1547,10 +1573,6 @@ int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, voi
 
   ProfScope ps(h, "bin", st);
   unsigned long long *status = h->d_status.as<unsigned long long>();
-  // status: [0] unlocated, [1] reaction slots, [2] slow-kernel molecules, [8 ..) counters of the molecules the
-  // records located
-  hipLaunchKernelGGL(k_clear_bin, dim3(grid1d(std::max<int64_t>(nc, 8 + kRouteSlots), 256)), dim3(256), 0, st,
-                     h->d_count.as<int32_t>(), nc, status, 8 + kRouteSlots);
   unsigned long long *routes = status + 8;
   // the previous binning of the same n (if any) gives the traversal order and the hints: its
   // permutation moves to d_perm_prev, and d_cell_sorted still holds its cells until rebuilt below
@@ -1558,6 +1580,11 @@ int aica_bin(aica_dil *h, const void *pos_dev, int32_t pos_dtype, int64_t n, voi
   h->perm_n = -1;
   if (prev) h->d_perm.swap(h->d_perm_prev);
   if ((rc = h->d_perm.ensure(4 * std::max<int64_t>(n, 1)))) return rc;
+  // status: [0] unlocated, [1] reaction slots, [2] slow-kernel molecules, [8 ..) counters of the molecules the
+  // records located
+  hipLaunchKernelGGL(k_clear_bin, dim3(grid1d(std::max<int64_t>(nc, 8 + kRouteSlots), 256)), dim3(256), 0, st,
+                     h->d_count.as<int32_t>(), nc, status, 8 + kRouteSlots, h->d_half.as<HalfFrames>(),
+                     BinRef{pos_dev, h->d_perm.as<int32_t>(), h->d_cell_sorted.as<int32_t>(), pos_dtype == AICA_FP64});
   const int32_t *trav = prev ? h->d_perm_prev.as<int32_t>() : nullptr;
   const int32_t *hint = prev ? h->d_cell_sorted.as<int32_t>() : nullptr;
   if (n > 0) {
@@ -1647,11 +1674,11 @@ static int build_tab(const aica_dil *h, const aica_params *p, LJTab &t) {
   t.rc2lo = (float)(t.rc2d - (double)t.band);
   t.rc2hi = (float)(t.rc2d + (double)t.band);
   // the square of a pair at about rc whose vector is off by at most err per axis, and the roundings of the square
-  auto near = [&](double half_ulp) {
-    const double err = half_ulp * h->frame_reach + h->frame_err;
+  auto near = [&](double half_ulp, double reach) {
+    const double err = half_ulp * reach + h->frame_err;
     return 3.5 * p->rcut * err + 3.0 * err * err + 16.0 * t.rc2d * half_ulp;
   };
-  const double n32 = near(std::ldexp(1.0, -24)), n64 = near(std::ldexp(1.0, -53));
+  const double n32 = near(std::ldexp(1.0, -24), h->frame_reach[0]), n64 = near(std::ldexp(1.0, -53), h->frame_reach[1]);
   t.near_lo = (float)(t.rc2d - n32);
   t.near_hi = (float)(t.rc2d + n32);
   t.near_lod = t.rc2d - n64;
@@ -1777,9 +1804,6 @@ static NbLists nb_lists(const aica_dil *h, int part) {
   nl.list = nullptr;
   nl.ng = h->nb.ng;
   nl.half = h->d_half.as<HalfFrames>();
-  nl.caller_pos = h->bin_pos;
-  nl.cell_of = h->d_cell_sorted.as<int32_t>();
-  nl.pos64 = h->bin_dtype == AICA_FP64;
   nl.i_off = h->d_nb_ioff.as<int64_t>();
   nl.i_mask = h->d_nb_imask.as<uint32_t>();
   if (h->geo.has_rot && part >= 0) {
