@@ -105,7 +105,9 @@ int aica_build_dil(const aica_mesh *mesh, double rcut, double guard, aica_dil **
  * test of Sec. 2.2 and App. A.1 (vertex-to-vertex distance below rcut + guard);
  * on distorted meshes it can miss cell pairs whose closest points are within
  * range while all their vertices are not (Sec. 2.2 on twisted meshes), and
- * then molecule pairs inside the cut-off go unevaluated.  Everything else as
+ * then molecule pairs inside the cut-off go unevaluated, in every call alike
+ * (which of them also depends on the interaction groups, and so on n: groups
+ * read whole cells for each other).  Everything else as
  * aica_build_dil (which is predicate AICA_DIL_CLOSEST).
  * Errors: as aica_build_dil, plus AICA_E_INVAL for an unknown predicate. */
 int aica_build_dil_ex(const aica_mesh *mesh, double rcut, double guard, int32_t predicate, aica_dil **out);
@@ -146,11 +148,13 @@ int aica_bin(aica_dil *dil, const void *pos_dev, int32_t pos_dtype, int64_t n, v
  * uw_dev: device double[2] = {U, W}, overwritten; npairs_dev: device int64,
  * overwritten.  Either may be NULL.  Results are deterministic (fixed
  * summation order, no atomics on forces).  With AICA_FP32 the cut-off is still
- * decided exactly for positions that are multiples of 2^-15 (pairs within
- * 2^-20 rc^2 of rc^2 are decided in FP64), except for images with a rotation:
+ * decided exactly for positions that are multiples of 2^-15 (pairs so close to
+ * rc^2 that FP32 rounding could decide are decided in FP64), except for images with a rotation:
  * a rotated position is formed in FP64 and kept as an FP32 value plus its FP32
  * remainder (the adjoint forms the pair vector from both), so only a pair
- * within about 1e-7 rc^2 of rc^2 may be decided either way.
+ * within about 1e-7 rc^2 of rc^2 may be decided either way.  Whatever the
+ * positions, all calls of one precision on one binning (forces, adjoint, pair
+ * export and counts) take the same pairs, and both molecules of a pair do.
  * Errors: AICA_E_INVAL, AICA_E_NOMEM, AICA_E_HIP. */
 int aica_forces(aica_dil *dil, const void *pos_dev, const int32_t *species_dev, const aica_params *params,
                 void *forces_dev, double *uw_dev, int64_t *npairs_dev, void *hip_stream);

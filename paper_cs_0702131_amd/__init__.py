@@ -230,8 +230,7 @@ def aica_pairs_export(dil: DIL, pos, rcut=None, precision="fp32"):
 
 
 def aica_pair_counts(dil: DIL, pos, rcut=None, precision="fp32"):
-    """Pairs inside the cut-off per molecule ([n] int32 on the device, caller order), from the traversal of
-    aica_forces."""
+    """Pairs inside the cut-off per molecule ([n] int32 on the device, caller order): those that aica_forces takes."""
     import torch
     _check_pos(pos)
     p, keep = _params(dil.rcut if rcut is None else rcut, (1.0,), (1.0,), precision, False)
