@@ -95,7 +95,7 @@ def measured_counters(kernel, workload):
     return out if digest == kernel_digest() else {}
 
 
-PAIR_KERNELS = {"pair_fwd": "k_force<float, 0, true, false>", "pair_adj": "k_force_adj<float, 0, false>"}
+PAIR_KERNELS = {"pair_fwd": "k_force<float, 0, true, false>", "pair_adj": "k_force_adj<float, 0, false, false>"}
 TIMERS = ("pair_fwd", "pair_adj", "bin", "finalize")
 
 
